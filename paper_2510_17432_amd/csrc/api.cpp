@@ -619,11 +619,12 @@ ChebPlan plan_cheb(std::vector<ChebInst>& insts, bool fp64, bool mom, int n_cu, 
     const int64_t n = (int64_t)I.Rg * I.n_strips * I.n_segs;
     const int ct = sparse ? I.ell_ct : 0;
     const int64_t nw = sparse ? I.n_segs * ceil_div(I.Rg, ct) : 0;
-    const bool honey = I.kind == CSP_HONEYCOMB, eps = I.eps != nullptr;
+    const bool honey = I.kind == CSP_HONEYCOMB;
+    const bool diag = I.eps != nullptr || I.beta0 != 0.0;
     const bool win = sparse && I.ellw_rows != nullptr;
-    if (p.runs.empty() || p.runs.back().honey != honey || p.runs.back().eps != eps ||
+    if (p.runs.empty() || p.runs.back().honey != honey || p.runs.back().diag != diag ||
         p.runs.back().sparse != sparse || p.runs.back().ct != ct || p.runs.back().win != win)
-      p.runs.push_back({(int)k, 0, t0, 0, honey, eps, sparse, ct, w0, 0, win, 0});
+      p.runs.push_back({(int)k, 0, t0, 0, honey, diag, sparse, ct, w0, 0, win, 0});
     p.runs.back().n_inst += 1;
     if (win)   // LDS values (window entries x columns) of the run's largest tile
       p.runs.back().win_cap = std::max<int64_t>(p.runs.back().win_cap,

@@ -163,11 +163,11 @@ struct ChebStep {
 };
 
 // Consecutive instances of one lattice class (honeycomb or not, with or
-// without on-site energies) and their work items; one launch per run.
+// without a diagonal) and their work items; one launch per run.
 struct ChebRun {
   int inst0, n_inst;
   int64_t item0, n_items;      // work items (stencil); moment records (explicit matrix)
-  bool honey, eps, sparse;
+  bool honey, diag, sparse;   // diag: on-site energies or H0 != 0
   int ct;                      // explicit matrix: columns per wave (workgroup if windowed)
   int64_t wave0, n_waves;      // explicit matrix: waves (workgroups if windowed) of the run
   bool win;                    // explicit matrix in the windowed layout

@@ -37,6 +37,21 @@
 // 2 nlev-row segment margins) and one write per level kept, instead of two
 // reads and one write per step.
 //
+// What bounds it.  On lattices whose vectors exceed the caches, HBM (rows in
+// flight: 5.4-6.0 TB/s).  On small and ordinary lattices there are one to
+// three waves per SIMD and a wave issues at most one instruction every four
+// cycles, so the instructions of a row iteration set the pace: the row loop
+// has no register moves (rows rotate by renaming), one 32-bit lane offset
+// for all stores with a scalar base per level, incremental row pointers with
+// one wrap, no tests in steady rows and one store region per iteration, and
+// strips over the seam of a periodic row take the same form.  Against the
+// form that moved rows, recomputed 64-bit addresses and ran seam strips
+// position by position (MI355X, per launch of 8 steps): 64 x 64 sites 30.4
+// -> 14.1 us (plain) and 38.5 -> 16 us (self products), graphene 1024^2 with
+// 4 columns and self products 102 -> 74 us, 16 uneven lattices of 64..512
+// sites a side 64 -> 30 us; bandwidth-bound launches (68 columns of graphene)
+// 2078 -> 2010 us.
+//
 // Moment variants (moment-based form of Sec. II.A).  MOM = kMomBra: for every
 // level and owned value the epilogue accumulates <psi0|phi_{n+l}>,
 // <psi0|phi_n> (first level only), <phi_{n+l}|phi_{n+l}> and
@@ -235,125 +250,205 @@ template <int V, int KT> struct Shape {
   static constexpr int OW = 64 * V - 2 * MG;          // owned positions per strip
 };
 
+// ---- value of lane l ^ M (M = 1, 2, 4, 8: DPP inside rows of 16 lanes)
+template <int M> __device__ __forceinline__ int xor_i(int x) {
+  if constexpr (M == 8) return __builtin_amdgcn_update_dpp(0, x, 0x128, 0xF, 0xF, true);
+  if constexpr (M == 4) {   // reversed inside 8, then inside 4
+    x = __builtin_amdgcn_update_dpp(0, x, 0x141, 0xF, 0xF, true);
+    return __builtin_amdgcn_update_dpp(0, x, 0x1B, 0xF, 0xF, true);
+  }
+  if constexpr (M == 2) return __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, true);
+  return __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, true);
+}
+// (a, b) -> {a of the lanes with bit M clear, b of those with it set} plus
+// the value of lane l ^ M: one step of a sum over the wave that keeps half
+// of the quantities in each half of the lanes
+template <int M> __device__ __forceinline__ float pair_sum(float a, float b, bool up) {
+  if constexpr (M >= 16) {
+    const unsigned ua = __builtin_bit_cast(unsigned, a), ub = __builtin_bit_cast(unsigned, b);
+    if constexpr (M == 32) {
+      const auto r = __builtin_amdgcn_permlane32_swap(ua, ub, false, false);
+      return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+    } else {
+      const auto r = __builtin_amdgcn_permlane16_swap(ua, ub, false, false);
+      return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
+    }
+  } else {
+    const float keep = up ? b : a, send = up ? a : b;
+    return keep + __builtin_bit_cast(float, xor_i<M>(__builtin_bit_cast(int, send)));
+  }
+}
+template <int M> __device__ __forceinline__ double pair_sum(double a, double b, bool up) {
+  const unsigned long long la = __builtin_bit_cast(unsigned long long, a);
+  const unsigned long long lb = __builtin_bit_cast(unsigned long long, b);
+  if constexpr (M >= 16) {
+    unsigned x0, x1, y0, y1;
+    if constexpr (M == 32) {
+      const auto r = __builtin_amdgcn_permlane32_swap((unsigned)la, (unsigned)lb, false, false);
+      const auto q = __builtin_amdgcn_permlane32_swap((unsigned)(la >> 32), (unsigned)(lb >> 32),
+                                                      false, false);
+      x0 = r[0]; y0 = r[1]; x1 = q[0]; y1 = q[1];
+    } else {
+      const auto r = __builtin_amdgcn_permlane16_swap((unsigned)la, (unsigned)lb, false, false);
+      const auto q = __builtin_amdgcn_permlane16_swap((unsigned)(la >> 32), (unsigned)(lb >> 32),
+                                                      false, false);
+      x0 = r[0]; y0 = r[1]; x1 = q[0]; y1 = q[1];
+    }
+    return __builtin_bit_cast(double, ((unsigned long long)x1 << 32) | x0) +
+           __builtin_bit_cast(double, ((unsigned long long)y1 << 32) | y0);
+  } else {
+    const double keep = up ? b : a;
+    const unsigned long long s = up ? la : lb;
+    const unsigned lo = (unsigned)xor_i<M>((int)(unsigned)s);
+    const unsigned hi = (unsigned)xor_i<M>((int)(unsigned)(s >> 32));
+    return keep + __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+  }
+}
+// Sum of every x[k] over the wave, pairs of lanes 32, 16, 8, 4, 2, 1 apart
+// added in that order (each quantity is added in the same order whatever
+// its index); quantity k ends in lane sum_lane<N>(k).  A plain butterfly
+// takes 6 N cross-lane moves; here each step halves the quantities a lane
+// holds (N = 16: 17 moves).
+template <int N, int M, typename T>
+__device__ __forceinline__ T wave_sums(T (&x)[N], int lane) {
+  constexpr int H = (N + 1) / 2;
+  T y[H];
+#pragma unroll
+  for (int k = 0; k < H; ++k) y[k] = pair_sum<M>(x[k], k + H < N ? x[k + H] : x[k], (lane & M) != 0);
+  if constexpr (M > 1) return wave_sums<H, M / 2>(y, lane);
+  else return y[0];
+}
+template <int N, int M = 32> __device__ __forceinline__ int sum_lane(int k) {
+  constexpr int H = (N + 1) / 2;
+  const int bit = k >= H ? M : 0;
+  if constexpr (M > 1) return bit + sum_lane<H, M / 2>(k >= H ? k - H : k);
+  else return bit;
+}
+
+// Marks a register row as holding nothing: the slots of a level that has
+// not started, or of a row that is not fetched, need not be kept (carrying
+// them through the skipped iterations cost a third slot per level, 24-30
+// VGPRs at 8 levels).
+template <typename T, int V> __device__ __forceinline__ void any_row(cx<T> (&d)[V]) {
+#pragma unroll
+  for (int v = 0; v < V; ++v) {
+    d[v].x = __builtin_nondeterministic_value(d[v].x);
+    d[v].y = __builtin_nondeterministic_value(d[v].y);
+  }
+}
+
 // insts: the instances of this launch (consecutive items item_lo..item_hi-1).
-template <typename T, int V, int KT, bool HONEY, bool EPS, int MOM, bool CARRY>
+// DIAG: the Hamiltonian has a diagonal (on-site energies, or H0 != 0).
+template <typename T, int V, int KT, bool HONEY, bool DIAG, int MOM, bool CARRY>
 __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts, int n_inst,
                                               int64_t item_lo, int64_t item_hi, ChebStep st) {
   static_assert(V % 2 == 0, "lanes hold whole (even, odd) orbital pairs");
   static_assert(!CARRY || MOM == kMomBra, "the carried state comes with the bra moments");
   using C = cx<T>;
   using gT = CSP_GLOBAL T;
+  using gB = CSP_GLOBAL char;
   constexpr int MG = Shape<V, KT>::MG;
   constexpr int OW = Shape<V, KT>::OW;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
   const int64_t item = item_lo + xcd_remap(blockIdx.x, gridDim.x) * 4 + wave;
   if (item >= item_hi) return;                     // a whole wave; no barriers below
-  int ii = 0;
-  while (ii + 1 < n_inst && item >= insts[ii + 1].item0) ++ii;
+  // the last instance whose first item is not past this one: 64 at a time
+  int ii = -1;
+  for (int k = 0; k < n_inst; k += 64)
+    ii += __popcll(__ballot(k + lane < n_inst && item >= insts[k + lane].item0));
   const ChebInst& I = insts[ii];
 
   // ---- geometry of this work item (wave-uniform)
+  const int n_strips = static_cast<int>(I.n_strips);
   const int64_t per_col = I.n_strips * I.n_segs;
   const int64_t local = item - I.item0;
-  const int64_t col = local / per_col;
-  const int64_t rem = local - col * per_col;
-  const int64_t seg = rem / I.n_strips;
-  const int64_t strip = rem - seg * I.n_strips;
+  int64_t col;
+  int rem;                                          // n_strips x n_segs <= N < 2^31
+  if (local < ((int64_t)1 << 31)) {
+    const unsigned c32 = static_cast<unsigned>(local) / static_cast<unsigned>(per_col);
+    col = c32;
+    rem = static_cast<int>(static_cast<unsigned>(local) - c32 * static_cast<unsigned>(per_col));
+  } else {
+    col = local / per_col;
+    rem = static_cast<int>(local - col * per_col);
+  }
+  const int seg = static_cast<int>(static_cast<unsigned>(rem) / static_cast<unsigned>(n_strips));
+  const int strip = rem - seg * n_strips;
   // positions, rows and offsets inside one lattice vector fit in 32 bits
   // (the host checks N < 2^31)
   const int opr = static_cast<int>(I.opr), Ly = static_cast<int>(I.Ly);
-  const int os = static_cast<int>(strip) * OW;       // first owned position
+  const int os = strip * OW;                         // first owned position
   const int p0 = os - MG;                            // first position of the strip
-  const bool fast = p0 >= 0 && p0 + 64 * V <= opr;   // no wrap, every position a site
-  const int y0 = static_cast<int>(seg) * st.seg_rows;
+  const int y0 = seg * st.seg_rows;
   const int y1 = (y0 + st.seg_rows < Ly) ? y0 + st.seg_rows : Ly;
+  const int H = y1 - y0;                             // owned rows
   const int nlev = st.nlev;
-  const int py = I.py;
+  const bool px = I.px != 0, py = I.py != 0;
   const int64_t coff = 2 * col * I.cstride;          // column offset in T units
-
-  // ---- per-lane positions
-  const int lq = V * lane;
-  const bool lane_own = lq >= MG && lq < MG + OW;
-  int wpos[V];          // position inside the row (wrapped), valid when present
-  bool pres[V];         // position is a site of the lattice
-  bool own[V];          // position owned by this strip
-#pragma unroll
-  for (int v = 0; v < V; ++v) {
-    const int p = p0 + lq + v;
-    if (I.px) {
-      int w = p % opr;
-      if (w < 0) w += opr;
-      wpos[v] = static_cast<int>(w);
-      pres[v] = true;
-    } else {
-      pres[v] = p >= 0 && p < opr;
-      wpos[v] = pres[v] ? static_cast<int>(p) : 0;
-    }
-    own[v] = lane_own && p >= 0 && p < opr;
-  }
-  auto row_of = [&](int r, bool& present) -> int {
-    if (py) {
-      while (r < 0) r += Ly;
-      while (r >= Ly) r -= Ly;
-      present = true;
-      return r;
-    }
-    present = static_cast<unsigned>(r) < static_cast<unsigned>(Ly);
-    return r;
-  };
-  // T offset of row rw (inside the lattice) in a column of the group's
-  // vectors (rows pitch values apart); the on-site energies are packed
   const int64_t pitch = I.pitch;
-  auto row_off = [&](int rw) -> int64_t { return 2 * static_cast<int64_t>(rw) * pitch; };
+  const int64_t pitchB = pitch * (int64_t)sizeof(C);
+  // iterations: the segment's rows and nlev margin rows on each side, in
+  // whole triples (the extra iterations compute rows past the segment, which
+  // are neither stored nor summed, from loads of rows that are inside the
+  // lattice or absent and read as zero)
+  const int n_iter = (H + 2 * nlev + 2) / 3 * 3;
+  const int rbase = y0 - nlev;                       // level-0 row of iteration 0
 
-  gT* base = (gT*)(I.base);
-  const gT* curv = (st.slot_cur < 0 ? (const gT*)(I.src)
-                                    : base + 2 * (int64_t)st.slot_cur * I.slot_stride) + coff;
-  const gT* prevv = st.first ? nullptr : base + 2 * (int64_t)st.slot_prev * I.slot_stride + coff;
-  gT* copyv = st.copy_slot >= 0 ? base + 2 * (int64_t)st.copy_slot * I.slot_stride + coff
-                                : nullptr;
+  // ---- per-lane positions.  Whole lanes: every lane's V positions are
+  // sites that follow each other in memory, after wrapping too, and are
+  // owned together; every row is inside the lattice after wrapping; and the
+  // segment spans less than 2^32 bytes.  True of strips inside a row, and of
+  // those over the seam of a periodic row of a multiple of V values, away
+  // from open edges: wide loads and stores at one 32-bit lane offset.
+  const int lq = V * lane;
+  const bool inside = p0 >= 0 && p0 + 64 * V <= opr;
+  const bool whole = (inside || (px && opr % V == 0)) &&
+                     (py || (rbase >= (CARRY ? nlev : 1) && rbase + n_iter <= Ly)) &&
+                     pitchB * (n_iter + 2) < ((int64_t)1 << 32);
+  const bool lane_in = lq >= MG && lq < MG + OW;
+
+  gB* base = (gB*)(I.base);
+  const int64_t slotB = I.slot_stride * (int64_t)sizeof(C);
+  const int64_t coffB = coff * (int64_t)sizeof(T);
+  const gB* curv =
+      (st.slot_cur < 0 ? (const gB*)(I.src) : base + st.slot_cur * slotB) + coffB;
+  const gB* prevv = st.first ? nullptr : base + st.slot_prev * slotB + coffB;
+  gB* copyv = st.copy_slot >= 0 ? base + st.copy_slot * slotB + coffB : nullptr;
   const gT* eps = (const gT*)(I.eps);
-  const gT* psi0 = (const gT*)(I.psi0) + coff;
-  gT* carry = CARRY && I.carry ? (gT*)(I.carry) + coff : nullptr;
+  const gB* psi0 = (const gB*)(I.psi0) + coffB;
+  gB* carry = CARRY && I.carry ? (gB*)(I.carry) + coffB : nullptr;
 
-  // output slot of each level (nullptr: not stored)
-  gT* outv[KT];
+  // output slot of each level (nullptr: not stored); the moment forms store
+  // the two newest levels of a launch only
+  gB* outv[KT];
 #pragma unroll
   for (int l = 0; l < KT; ++l)
-    outv[l] = st.slot_out[l] >= 0 ? base + 2 * (int64_t)st.slot_out[l] * I.slot_stride + coff
-                                  : nullptr;
+    outv[l] = st.slot_out[l] >= 0 ? base + st.slot_out[l] * slotB + coffB : nullptr;
 
-  // ---- register rows: rr[l][.] = the last three rows of level l.  With ROT
-  // (the self-product kernel, whose pace is set by its instruction count)
-  // the three slots rotate with the row index: before an iteration of phase
+  // ---- register rows: rr[l][.] = the last three rows of level l.  The
+  // three slots rotate with the row index: before an iteration of phase
   // P = i mod 3, slot P holds the oldest row, P + 1 the middle and P + 2 the
   // newest; the iteration overwrites slot P with the new row, and the row
   // loop is unrolled by three so every slot index is a constant (rotation by
-  // renaming, no register moves).  Without ROT every iteration moves the
-  // rows down one slot and writes the new row into slot 2.  At 8 steps per
-  // launch only the honeycomb lattice without on-site energies rotates:
-  // unrolled, the others take 186-214 VGPRs (2 waves per SIMD instead of 3).
-  constexpr bool ROT = MOM == kMomSelf && (KT <= 4 || (HONEY && !EPS));
+  // renaming, no register moves).
   C rr[KT][3][V];
 #pragma unroll
   for (int l = 0; l < KT; ++l)
 #pragma unroll
-    for (int k = 0; k < 3; ++k)
+    for (int k = 0; k < 3; ++k) any_row(rr[l][k]);
+  T br[DIAG ? KT + 1 : 1][V];                        // diagonal of 2 H~ in rows r0 - k
 #pragma unroll
-      for (int v = 0; v < V; ++v) rr[l][k][v] = {T(0), T(0)};
-  T er[EPS ? KT + 1 : 1][V];                         // on-site energies of rows r0 - k
+  for (int k = 0; k < (DIAG ? KT + 1 : 1); ++k)
 #pragma unroll
-  for (int k = 0; k < (EPS ? KT + 1 : 1); ++k)
-#pragma unroll
-    for (int v = 0; v < V; ++v) er[k][v] = T(0);
+    for (int v = 0; v < V; ++v) br[k][v] = T(0);
 
   // Moment sums.  kMomBra: quantity q = 5 (l - 1) + j for level l: j = 0, 1
   // <psi0|out>, 2 |out|^2, 3, 4 <out|cur>; q = 5 KT + 0, 1: <psi0|cur> of
   // the first level.  kMomSelf: q = 2 (l - 1) + j: j = 0 |out|^2, 1
   // Re <out|cur>.  sq holds this lane's working-precision sums of the last
   // rows; every kFlush rows each is summed over the wave and added in FP64
-  // into accq of lane q.
+  // into accq of lane sum_lane(q).
   constexpr int kFlush = 16;
   constexpr int NQ = MOM == kMomBra ? 5 * KT + 2 : (MOM == kMomSelf ? 2 * KT : 1);
   T sq[NQ];
@@ -378,119 +473,172 @@ __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts
 #pragma unroll
     for (int v = 0; v < V; ++v) cpr[k][v] = {T(0), T(0)};
 
+  // phi_{n+l} = alpha (sum of neighbours) + (diagonal phi_{n+l-1} - phi_{n+l-2});
+  // the first step of a block takes half of both coefficients (exact)
   const T alpha = static_cast<T>(I.alpha);
   const T beta0 = static_cast<T>(I.beta0);
   const T oscale = static_cast<T>(I.onsite_scale);
-  const bool vert = I.kind != CSP_CHAIN;
-  // iterations: the segment's rows and nlev margin rows on each side; with
-  // ROT rounded up to a multiple of three (the extra iterations compute rows
-  // past the segment, which are neither stored nor summed, from loads of
-  // rows that are inside the lattice or absent and read as zero)
-  const int n_iter = ROT ? ((y1 - y0) + 2 * nlev + 2) / 3 * 3 : (y1 - y0) + 2 * nlev;
-  const int rbase = y0 - nlev;                       // level-0 row of iteration 0
+  const T half1 = st.first ? T(0.5) : T(1);
+  const T alpha1 = half1 * alpha;
 
-  // The row loop, compiled twice: FAST for strips inside the row (no wrap,
-  // every position a site: wide loads and stores, whole lanes owned), and
-  // the general form with per-position wrap, presence and ownership.
-  auto run = [&](auto fast_tag) {
-    constexpr bool FAST = decltype(fast_tag)::value;
-    auto load_row = [&](const gT* vec, int r, C (&d)[V]) {
-      bool rp;
-      const int rw = row_of(r, rp);
-      if (!rp) {
-#pragma unroll
-        for (int v = 0; v < V; ++v) d[v] = {T(0), T(0)};
-        return;
+  // Rows loaded ahead of their use: with one wave per SIMD (small lattices)
+  // an iteration takes less time than a load from HBM, so the plain and
+  // self-product forms keep three rows in flight, one per phase; the forms
+  // that also read psi0 or the carried state, one.
+  constexpr int PF = MOM == kMomBra ? 1 : 3;
+
+  auto run = [&](auto whole_tag) {
+    constexpr bool WHOLE = decltype(whole_tag)::value;
+    // general form: positions one by one
+    int wpos[V];          // position inside the row (wrapped), valid when present
+    bool pres[V];         // position is a site of the lattice
+    bool own[V];          // position owned by this strip
+    unsigned lb = 0;      // WHOLE: byte offset of the lane's values in a row
+    bool lane_own = lane_in;
+    if constexpr (WHOLE) {
+      int w = p0 + lq;
+      lane_own = lane_in && w < opr;
+      if (!inside) {
+        w %= opr;
+        if (w < 0) w += opr;
       }
-      const gT* rowp = vec + row_off(rw);
-      if constexpr (FAST) {
-        ldv<V>(rowp + 2 * p0 + 2 * lq, d);
-      } else {
+      lb = static_cast<unsigned>(w) * static_cast<unsigned>(sizeof(C));
+    } else {
 #pragma unroll
-        for (int v = 0; v < V; ++v) d[v] = pres[v] ? ld1(rowp + 2 * wpos[v]) : C{T(0), T(0)};
-      }
-    };
-    auto load_eps = [&](int r, T (&d)[V]) {
-      bool rp;
-      const int rw = row_of(r, rp);
-      if (!rp) {
-#pragma unroll
-        for (int v = 0; v < V; ++v) d[v] = T(0);
-        return;
-      }
-      const gT* rowp = eps + static_cast<int64_t>(rw) * opr;
-      if constexpr (FAST) {
-        ldr<V>(rowp + p0 + lq, d);
-      } else {
-#pragma unroll
-        for (int v = 0; v < V; ++v) d[v] = pres[v] ? rowp[wpos[v]] : T(0);
-      }
-    };
-    // row rw must be inside [0, Ly); nt: non-temporal (Chebyshev slots)
-    auto store_row = [&](gT* vec, int rw, const C (&o)[V], bool nt) {
-      gT* rowp = vec + row_off(rw);
-      if constexpr (FAST) {
-        if (lane_own) {
-          if (nt) stv_nt<V>(rowp + 2 * p0 + 2 * lq, o);
-          else stv<V>(rowp + 2 * p0 + 2 * lq, o);
+      for (int v = 0; v < V; ++v) {
+        const int p = p0 + lq + v;
+        if (px) {
+          int w = p % opr;
+          if (w < 0) w += opr;
+          wpos[v] = w;
+          pres[v] = true;
+        } else {
+          pres[v] = p >= 0 && p < opr;
+          wpos[v] = pres[v] ? p : 0;
         }
+        own[v] = lane_in && p >= 0 && p < opr;
+      }
+    }
+    auto load_row = [&](const gB* rowp, bool rp, C (&d)[V]) {
+      if constexpr (WHOLE) {
+        ldv<V>((const gT*)(rowp + lb), d);
       } else {
 #pragma unroll
         for (int v = 0; v < V; ++v)
-          if (own[v]) st1(rowp + 2 * wpos[v], o[v]);
+          d[v] = rp && pres[v] ? ld1((const gT*)rowp + 2 * (int64_t)wpos[v]) : C{T(0), T(0)};
       }
     };
-
-    C ncur[V], nprev[V], pv[V], npq[V], ncar[V], car[V];
-    T neps[V];
+    auto store_row = [&](gB* rowp, const C (&o)[V]) {
 #pragma unroll
-    for (int v = 0; v < V; ++v) {
-      nprev[v] = {T(0), T(0)};
-      npq[v] = {T(0), T(0)};
-      ncar[v] = {T(0), T(0)};
+      for (int v = 0; v < V; ++v)
+        if (own[v]) st1((gT*)rowp + 2 * (int64_t)wpos[v], o[v]);
+    };
+    // WHOLE: rows are written at base[level] + i pitchB + lane offset
+    // (32 bits), base[l] = the level's row of iteration 0
+    gB* outb[KT];
+    gB* copyb = copyv + (int64_t)rbase * pitchB;
+    gB* carryb = carry + (int64_t)(rbase - nlev) * pitchB;
+#pragma unroll
+    for (int l = 1; l <= KT; ++l) outb[l - 1] = outv[l - 1] + (int64_t)(rbase - l) * pitchB;
+    unsigned so = lb;                                // lb + i pitchB
+
+    C nc[PF][V], np[PF][V], nq[MOM == kMomBra ? PF : 1][V], nk[CARRY ? PF : 1][V];
+    T ne[DIAG ? PF : 1][V];
+    C pv[V], car[V];
+#pragma unroll
+    for (int k = 0; k < PF; ++k)
+#pragma unroll
+      for (int v = 0; v < V; ++v) np[k][v] = {T(0), T(0)};
+    // next row to load: index (wrapped in a periodic lattice) and byte
+    // offset; the row before it (phi_{n-1} lags one row, the carried state
+    // nlev rows)
+    int lrow = rbase;
+    if (py) {
+      lrow %= Ly;
+      if (lrow < 0) lrow += Ly;
     }
-    load_row(curv, rbase, ncur);
-    if (prevv) load_row(prevv, rbase - 1, nprev);
-    if constexpr (EPS) load_eps(rbase, neps);
-    if (want_psi0) load_row(psi0, rbase, npq);
-    if (carry_in) load_row(carry, rbase - nlev, ncar);
+    int64_t lo = lrow * pitchB;
+    int prow = lrow - 1;
+    if (py && prow < 0) prow += Ly;
+    int64_t po = prow * pitchB;
+    int krow = lrow - nlev;
+    if (CARRY && py) {
+      krow %= Ly;
+      if (krow < 0) krow += Ly;
+    }
+    int64_t ko = krow * pitchB;
+    auto owned_row = [&](int k) { return static_cast<unsigned>(k) < static_cast<unsigned>(H); };
+    auto row_in = [&](int r) { return static_cast<unsigned>(r) < static_cast<unsigned>(Ly); };
+    auto fetch = [&](auto slot_tag) {
+      constexpr int B = decltype(slot_tag)::value;
+      const bool rp = WHOLE || row_in(lrow);
+      load_row(curv + lo, rp, nc[B]);
+      if (prevv) load_row(prevv + po, WHOLE || row_in(prow), np[B]);
+      if constexpr (DIAG) {
+        if (!eps) {
+#pragma unroll
+          for (int v = 0; v < V; ++v) ne[B][v] = T(0);
+        } else {
+          const gT* rowp = eps + (int64_t)lrow * opr;
+          if constexpr (WHOLE) {
+            ldr<V>((const gT*)((const gB*)rowp + lb / 2), ne[B]);
+          } else {
+#pragma unroll
+            for (int v = 0; v < V; ++v) ne[B][v] = rp && pres[v] ? rowp[wpos[v]] : T(0);
+          }
+        }
+      }
+      if constexpr (MOM == kMomBra)
+        if (want_psi0) load_row(psi0 + lo, rp, nq[B]);
+      if constexpr (CARRY) {
+        if (carry_in) load_row(carry + ko, WHOLE || row_in(krow), nk[B]);
+        ++krow;
+        ko += pitchB;
+        if (py && krow == Ly) {
+          krow = 0;
+          ko = 0;
+        }
+      }
+      prow = lrow;
+      po = lo;
+      ++lrow;
+      lo += pitchB;
+      if (py && lrow == Ly) {
+        lrow = 0;
+        lo = 0;
+      }
+    };
+    fetch(std::integral_constant<int, 0>{});
+    if constexpr (PF == 3) {
+      fetch(std::integral_constant<int, 1>{});
+      fetch(std::integral_constant<int, 2>{});
+    }
 
     int flush_in = kFlush;                           // rows left before the next flush
     // one iteration: level 0 takes row r0 = rbase + i, level l computes row
     // r0 - l; the phase selects the register slots.  STEADY iterations are
     // those in which all KT levels run and compute rows of the segment
-    // (i in [2 KT, H + KT + 1) with nlev = KT): no level or row tests, and
-    // those rows are inside the lattice.
+    // (i in [2 KT, H + KT + 1) with nlev = KT): no level or row tests.
+    // Launches that copy phi_n have none.
     auto iter = [&](auto phase_tag, auto steady_tag, int i) {
-      constexpr int P = ROT ? decltype(phase_tag)::value : 2;
+      constexpr int P = decltype(phase_tag)::value;
       constexpr bool STEADY = decltype(steady_tag)::value;
       // slots after this iteration's new rows: oldest, middle, newest
       constexpr int SLO = (P + 1) % 3, SMI = (P + 2) % 3, SHI = P;
-      // without ROT a level moves its rows down one slot before it writes
-      // its new row
-      auto shift_down = [&](int l) {
-        if constexpr (!ROT) {
-#pragma unroll
-          for (int v = 0; v < V; ++v) {
-            rr[l][0][v] = rr[l][1][v];
-            rr[l][1][v] = rr[l][2][v];
-          }
-        }
-      };
+      constexpr int B = PF == 3 ? P : 0;
       const int r0 = rbase + i;
-      shift_down(0);
 #pragma unroll
       for (int v = 0; v < V; ++v) {
-        rr[0][SHI][v] = ncur[v];
-        pv[v] = nprev[v];
+        rr[0][SHI][v] = nc[B][v];
+        pv[v] = np[B][v];
       }
-      if constexpr (EPS) {
+      if constexpr (DIAG) {
 #pragma unroll
         for (int k = KT; k >= 1; --k)
 #pragma unroll
-          for (int v = 0; v < V; ++v) er[k][v] = er[k - 1][v];
+          for (int v = 0; v < V; ++v) br[k][v] = br[k - 1][v];
 #pragma unroll
-        for (int v = 0; v < V; ++v) er[0][v] = neps[v];
+        for (int v = 0; v < V; ++v) br[0][v] = beta0 + oscale * ne[B][v];
       }
       if constexpr (MOM == kMomBra) {
 #pragma unroll
@@ -498,12 +646,11 @@ __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts
 #pragma unroll
           for (int v = 0; v < V; ++v) pq[k][v] = pq[k - 1][v];
 #pragma unroll
-        for (int v = 0; v < V; ++v) {
-          pq[0][v] = npq[v];
-          car[v] = ncar[v];
-        }
+        for (int v = 0; v < V; ++v) pq[0][v] = nq[B][v];
       }
       if constexpr (CARRY) {
+#pragma unroll
+        for (int v = 0; v < V; ++v) car[v] = nk[B][v];
 #pragma unroll
         for (int k = KT - 1; k >= 1; --k)
 #pragma unroll
@@ -511,84 +658,98 @@ __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts
 #pragma unroll
         for (int v = 0; v < V; ++v) cpr[0][v] = {T(0), T(0)};
       }
-      if (i + 1 < n_iter) {
-        load_row(curv, r0 + 1, ncur);
-        if (prevv) load_row(prevv, r0, nprev);
-        if constexpr (EPS) load_eps(r0 + 1, neps);
-        if (want_psi0) load_row(psi0, r0 + 1, npq);
-        if (carry_in) load_row(carry, r0 + 1 - nlev, ncar);
+      // (a steady iteration of four or more levels always has PF rows to go)
+      if ((STEADY && KT > PF) || i + PF < n_iter) {
+        fetch(std::integral_constant<int, B>{});
+      } else {
+        any_row(nc[B]);
+        if (prevv) any_row(np[B]);
       }
-      // phi_n itself for the contraction (order 0 of a block)
-      if (copyv && r0 >= y0 && r0 < y1) store_row(copyv, r0, rr[0][SHI], true);
+      // phi_n itself for the contraction (order 0 of a block; no steady form)
+      if (!STEADY && copyv && owned_row(i - nlev)) {
+        if constexpr (WHOLE) {
+          if (lane_own) stv_nt<V>((gT*)(copyb + so), rr[0][SHI]);
+        } else {
+          store_row(copyv + (int64_t)r0 * pitchB, rr[0][SHI]);
+        }
+      }
+      C olast[V];                                    // level KT (the others are in rr)
+      // levels that have their three input rows
+      const int lmax = i / 2 < nlev ? i / 2 : nlev;
 
 #pragma unroll
       for (int l = 1; l <= KT; ++l) {
         if constexpr (!STEADY) {
-          if (l > nlev || i < 2 * l) break;
+          if (l > lmax) {                            // not started: any contents
+            if (l < KT) any_row(rr[l < KT ? l : 0][SHI]);
+            else any_row(olast);
+            continue;
+          }
         }
         const int r = r0 - l;
-        bool rp = true;
-        const int rw = STEADY ? r : row_of(r, rp);
-        // With ROT a row outside the lattice (rp false) gets zero
-        // coefficients: its phi_{n+l-1} and phi_{n+l-2} rows are zero, so o
-        // is zero without a branch.  The other kernels branch (measured
-        // faster there).
-        const T scale = (ROT && !rp) ? T(0) : ((l == 1 && st.first) ? T(0.5) : T(1));
-        const T as = scale * alpha, bs = scale * beta0, os_ = scale * oscale;
+        // a row outside an open lattice is zero: its neighbours count for
+        // nothing and its own rows of the two levels before are zero
+        T as = l == 1 ? alpha1 : alpha;
+        if constexpr (!WHOLE)
+          if (!py && !row_in(r)) as = T(0);
         // level l-1 rows r - 1, r, r + 1 and level l-2 row r (phi_{n+l-2})
         const C(&up)[V] = rr[l - 1][SLO];
         const C(&c)[V] = rr[l - 1][SMI];
         const C(&dn)[V] = rr[l - 1][SHI];
         C o[V];
-        if (ROT || rp) {
-          const T lx = shr1(c[V - 1].x), ly = shr1(c[V - 1].y);
-          const T rx = shl1(c[0].x), ry = shl1(c[0].y);
+        const T lx = shr1(c[V - 1].x), ly = shr1(c[V - 1].y);
+        const T rx = shl1(c[0].x), ry = shl1(c[0].y);
 #pragma unroll
-          for (int v = 0; v < V; ++v) {
-            T nx = (v > 0 ? c[v - 1].x : lx) + (v < V - 1 ? c[v + 1].x : rx);
-            T ny = (v > 0 ? c[v - 1].y : ly) + (v < V - 1 ? c[v + 1].y : ry);
-            if constexpr (HONEY) {
-              // even orbital: partner one row up (pos + 1); odd: one row down (pos - 1)
-              if (v % 2 == 0) {
-                nx += up[v + 1].x;
-                ny += up[v + 1].y;
-              } else {
-                nx += dn[v - 1].x;
-                ny += dn[v - 1].y;
-              }
+        for (int v = 0; v < V; ++v) {
+          T nx = (v > 0 ? c[v - 1].x : lx) + (v < V - 1 ? c[v + 1].x : rx);
+          T ny = (v > 0 ? c[v - 1].y : ly) + (v < V - 1 ? c[v + 1].y : ry);
+          if constexpr (HONEY) {
+            // even orbital: partner one row up (pos + 1); odd: one row down (pos - 1)
+            if (v % 2 == 0) {
+              nx += up[v + 1].x;
+              ny += up[v + 1].y;
             } else {
-              if (vert) {
-                nx += up[v].x + dn[v].x;
-                ny += up[v].y + dn[v].y;
-              }
+              nx += dn[v - 1].x;
+              ny += dn[v - 1].y;
             }
-            const C p = l == 1 ? pv[v] : rr[l - 2 >= 0 ? l - 2 : 0][SLO][v];
-            T beta = bs;
-            if constexpr (EPS) beta = bs + os_ * er[l][v];
+          } else {
+            // (a chain's rows -1 and 1 are absent: zero)
+            nx += up[v].x + dn[v].x;
+            ny += up[v].y + dn[v].y;
+          }
+          const C p = l == 1 ? pv[v] : rr[l - 2 >= 0 ? l - 2 : 0][SLO][v];
+          if constexpr (DIAG) {
+            const T beta = l == 1 ? half1 * br[1][v] : br[l][v];
             o[v].x = as * nx + (beta * c[v].x - p.x);
             o[v].y = as * ny + (beta * c[v].y - p.y);
+          } else {
+            o[v].x = as * nx - p.x;
+            o[v].y = as * ny - p.y;
           }
-          if constexpr (!FAST) {
+        }
+        if constexpr (!WHOLE) {
 #pragma unroll
-            for (int v = 0; v < V; ++v)
-              if (!pres[v]) o[v] = {T(0), T(0)};
-          }
-        } else {
-#pragma unroll
-          for (int v = 0; v < V; ++v) o[v] = {T(0), T(0)};
+          for (int v = 0; v < V; ++v)
+            if (!pres[v]) o[v] = {T(0), T(0)};
         }
         if (l < KT) {
-          shift_down(l);
 #pragma unroll
           for (int v = 0; v < V; ++v) rr[l][SHI][v] = o[v];
         }
-        if (STEADY || (r >= y0 && r < y1)) {
-          if (outv[l - 1]) store_row(outv[l - 1], rw, o, true);
+        if constexpr (WHOLE) {
+          if (l == KT) {
+#pragma unroll
+            for (int v = 0; v < V; ++v) olast[v] = o[v];
+          }
+        }
+        if (STEADY || owned_row(i - nlev - l)) {
+          if constexpr (!WHOLE)
+            if (MOM == kMomNone || l >= nlev - 1) store_row(outv[l - 1] + (int64_t)r * pitchB, o);
           if constexpr (MOM == kMomSelf) {
             const int q0 = 2 * (l - 1);
 #pragma unroll
             for (int v = 0; v < V; ++v) {
-              const bool w = FAST ? true : own[v];
+              const bool w = WHOLE ? true : own[v];
               const C oo = w ? o[v] : C{T(0), T(0)};
               // one accumulating FMA per product
               sq[q0] += oo.x * oo.x;
@@ -600,12 +761,11 @@ __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts
           if constexpr (MOM == kMomBra) {
             if (dots) {
               // values outside the owned positions take no part in the sums
-              // (interior strips: whole lanes, masked when the sums are
-              // flushed)
+              // (whole lanes: masked when the sums are flushed)
               C oo[V], cc[V];
 #pragma unroll
               for (int v = 0; v < V; ++v) {
-                const bool w = FAST ? true : own[v];
+                const bool w = WHOLE ? true : own[v];
                 oo[v] = w ? o[v] : C{T(0), T(0)};
                 cc[v] = w ? c[v] : C{T(0), T(0)};
               }
@@ -662,55 +822,64 @@ __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts
                     b[v].y += car[v].y;
                   }
                 }
-                store_row(carry, rw, b, false);
+                if constexpr (WHOLE) {
+                  if (lane_own) stv<V>((gT*)(carryb + so), b);
+                } else {
+                  store_row(carry + (int64_t)r * pitchB, b);
+                }
               }
             }
           }
         }
       }
+      // Whole lanes are stored after all levels, so that one test of the
+      // lane covers them and the level loop is straight-line code
+      if constexpr (WHOLE) {
+        if (lane_own) {
+#pragma unroll
+          for (int l = 1; l <= KT; ++l) {
+            if constexpr (STEADY) {
+              if (MOM != kMomNone && l < KT - 1) continue;
+            } else {
+              if (l > lmax) break;
+              if (!owned_row(i - nlev - l) || (MOM != kMomNone && l < nlev - 1)) continue;
+            }
+            if (l < KT) stv_nt<V>((gT*)(outb[l - 1] + so), rr[l < KT ? l : 0][SHI]);
+            else stv_nt<V>((gT*)(outb[l - 1] + so), olast);
+          }
+        }
+        so += static_cast<unsigned>(pitchB);
+      }
       if constexpr (MOM != kMomNone) {
         if (dots && (--flush_in == 0 || i + 1 == n_iter)) {
           flush_in = kFlush;
+          T x[NQ];
 #pragma unroll
           for (int k = 0; k < NQ; ++k) {
-            T x = (FAST && !lane_own) ? T(0) : sq[k];
-#pragma unroll
-            for (int m = 32; m >= 1; m >>= 1) x += __shfl_xor(x, m);
-            if (lane == k) accq += static_cast<double>(x);
+            x[k] = (WHOLE && !lane_own) ? T(0) : sq[k];
             sq[k] = T(0);
           }
+          accq += static_cast<double>(wave_sums<NQ, 32>(x, lane));
         }
       }
     };
-    // iterations [i0, i1) (with ROT multiples of three)
+    // iterations [i0, i1), multiples of three
     auto iter_range = [&](auto steady_tag, int i0, int i1) {
-      if constexpr (ROT) {
 #pragma unroll 1
-        for (int i = i0; i < i1; i += 3) {
-          iter(std::integral_constant<int, 0>{}, steady_tag, i);
-          iter(std::integral_constant<int, 1>{}, steady_tag, i + 1);
-          iter(std::integral_constant<int, 2>{}, steady_tag, i + 2);
-        }
-      } else {
-#pragma unroll 1
-        for (int i = i0; i < i1; ++i) iter(std::integral_constant<int, 2>{}, steady_tag, i);
+      for (int i = i0; i < i1; i += 3) {
+        iter(std::integral_constant<int, 0>{}, steady_tag, i);
+        iter(std::integral_constant<int, 1>{}, steady_tag, i + 1);
+        iter(std::integral_constant<int, 2>{}, steady_tag, i + 2);
       }
     };
-    // steady iterations [ia, ib), rounded inwards to multiples of three
-    // with ROT; the others take the general form.  Only the ROT kernels
-    // have a steady form: in the others a second copy of the row loop costs
-    // registers (occupancy) that the shorter scalar path does not repay.
-    int ia = n_iter, ib = n_iter;
-    if (nlev == KT) {
-      ia = 2 * KT;
-      ib = (y1 - y0) + KT + 1;
-      if constexpr (ROT) {
-        ia = (ia + 2) / 3 * 3;
-        ib = ib / 3 * 3;
+    if constexpr (WHOLE) {
+      // steady iterations [ia, ib), rounded inwards to multiples of three
+      int ia = n_iter, ib = n_iter;
+      if (nlev == KT && !copyv) {
+        ia = (2 * KT + 2) / 3 * 3;
+        ib = (H + KT + 1) / 3 * 3;
+        if (ib < ia) ia = ib = n_iter;
       }
-      if (ib < ia) ib = ia;
-    }
-    if constexpr (ROT) {
       iter_range(std::false_type{}, 0, ia);
       iter_range(std::true_type{}, ia, ib);
       iter_range(std::false_type{}, ib, n_iter);
@@ -718,7 +887,7 @@ __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts
       iter_range(std::false_type{}, 0, n_iter);
     }
   };
-  if (fast) run(std::true_type{});
+  if (whole) run(std::true_type{});
   else run(std::false_type{});
 
   if constexpr (MOM != kMomNone) {
@@ -739,7 +908,7 @@ __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts
         else if (slot == 6 || slot == 7) q = 5 * l + slot - 3;
         else if ((slot == 2 || slot == 3) && l == 0) q = 5 * KT + slot - 2;
       }
-      const double val = __shfl(accq, q < 0 ? 0 : q);
+      const double val = __shfl(accq, q < 0 || q >= NQ ? 0 : sum_lane<NQ>(q));
       if (l < nlev && l < KT) {
         double* out = st.partial + (((int64_t)st.mom_slot * KT + l) * st.total_items + item) * 8;
         out[slot] = q < 0 ? 0.0 : val;
@@ -756,13 +925,13 @@ __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts
 #define CSP_CHEB_LAUNCH(T, V, KT, MOM, CARRY)                                                  \
   do {                                                                                         \
     if (honey) {                                                                               \
-      if (eps) hipLaunchKernelGGL((cheb::k_cheb<T, V, KT, true, true, MOM, CARRY>), grid,      \
-                                  block, 0, s, d_inst, n_inst, item_lo, item_hi, st);          \
+      if (diag) hipLaunchKernelGGL((cheb::k_cheb<T, V, KT, true, true, MOM, CARRY>), grid,     \
+                                   block, 0, s, d_inst, n_inst, item_lo, item_hi, st);         \
       else hipLaunchKernelGGL((cheb::k_cheb<T, V, KT, true, false, MOM, CARRY>), grid, block,  \
                               0, s, d_inst, n_inst, item_lo, item_hi, st);                     \
     } else {                                                                                   \
-      if (eps) hipLaunchKernelGGL((cheb::k_cheb<T, V, KT, false, true, MOM, CARRY>), grid,     \
-                                  block, 0, s, d_inst, n_inst, item_lo, item_hi, st);          \
+      if (diag) hipLaunchKernelGGL((cheb::k_cheb<T, V, KT, false, true, MOM, CARRY>), grid,    \
+                                   block, 0, s, d_inst, n_inst, item_lo, item_hi, st);         \
       else hipLaunchKernelGGL((cheb::k_cheb<T, V, KT, false, false, MOM, CARRY>), grid, block, \
                               0, s, d_inst, n_inst, item_lo, item_hi, st);                     \
     }                                                                                          \
