@@ -1308,9 +1308,10 @@ static csp_status propagate_impl(csp_context* c, const std::vector<InstIn>& ins,
   // ---------------------------------------------------------- instance tables
   std::vector<ContractInst> ct;
   std::vector<FinishInst> fi;
-  int wg0 = 0;
+  int wg0 = 0, rg_max = 1;
   for (size_t gi = 0; gi < groups.size(); ++gi) {
     const Group& g = groups[gi];
+    rg_max = std::max(rg_max, g.Rg);
     const InstIn& in = ins[g.inst];
     ChebInst& I = sp[gi];
     I.base = g.slots;
@@ -1429,7 +1430,7 @@ static csp_status propagate_impl(csp_context* c, const std::vector<InstIn>& ins,
       produced += stb.nlev;
       CHECK(run_chunks());
     }
-    HIPCALL(launch_finish(d_fin, (int)fi.size(), bk, t0, from_dev ? d_blk : nullptr, strm));
+    HIPCALL(launch_finish(d_fin, (int)fi.size(), bk, rg_max, t0, from_dev ? d_blk : nullptr, strm));
     if (P.check_norm) {
       for (auto& g : groups) {
         const InstIn& in = ins[g.inst];
@@ -1820,7 +1821,7 @@ static csp_status propagate_moments_impl(csp_context* c, const std::vector<InstI
       prev_slot = new_prev;
       ++launches;
       if (launches == P_batch || produced >= steps) {
-        HIPCALL(launch_cheb_mom_finish(d_mi, (int)mi.size(), d_part, sp_plan.total_items, kt,
+        HIPCALL(launch_cheb_mom_finish(d_mi, (int)mi.size(), rmax, d_part, sp_plan.total_items, kt,
                                        launches, batch0, produced, s));
         batch0 = produced + 1;
         launches = 0;

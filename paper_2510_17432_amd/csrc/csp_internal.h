@@ -225,9 +225,9 @@ struct MomInst {
   int32_t Rg, pad;
   double* dots;                // [n_rows][4][Rg] complex
 };
-hipError_t launch_cheb_mom_finish(const MomInst* d_mi, int n_inst, const double* partial,
-                                  int64_t total_items, int kt, int n_slots, int n0, int max_row,
-                                  hipStream_t s);
+hipError_t launch_cheb_mom_finish(const MomInst* d_mi, int n_inst, int rg_max,
+                                  const double* partial, int64_t total_items, int kt, int n_slots,
+                                  int n0, int max_row, hipStream_t s);
 // Moments of a block from the step sums (halving: every moment above mu_1 from the self products)
 // and correlations corr[(t0 + j) * ldc + col0 + r] = sum_n c_n(j tau) mu_n[r]
 // for j = 1..bk (table a as produced by launch_bessel, row j-1 for x = j tau).
@@ -349,7 +349,8 @@ struct FinishInst {
   int32_t pad;
 };
 // t0_dev (may be null): device copy of t0, read at run time (graph replays).
-hipError_t launch_finish(const FinishInst* d_inst, int n_inst, int bcols, int64_t t0,
+// rg_max: most columns of an instance.
+hipError_t launch_finish(const FinishInst* d_inst, int n_inst, int bcols, int rg_max, int64_t t0,
                          const int64_t* t0_dev, hipStream_t s);
 // d_blk[0] += b, d_blk[1] += 1 (the block counter of graph replays).
 hipError_t launch_advance(int64_t* d_blk, int64_t b, hipStream_t s);
@@ -412,7 +413,7 @@ hipError_t launch_qe_scatter(int64_t N, int Rg, int nE, int ld, int col0, bool f
 // ------------------------------------------------------------------ coefficients
 // For x_j = (j + 1) * tau, j = 0..nx-1: a[j][n] = J_n(x_j) (n = 0) or
 // 2 J_n(x_j) (n >= 1) for n <= nmax, and ntrunc[j] = N(x_j).  clip: orders
-// beyond x_j + 40 + 25 x_j^(1/3) (past the truncation) are stored as 0.
+// beyond x_j + 40 + 25 x_j^(1/3) (past the truncation) are not stored.
 hipError_t launch_bessel(double tau, int nx, int nmax, double eta, bool clip, double* d_a,
                          int32_t* d_ntrunc, hipStream_t s);
 // Complex c_n(x) = (-i)^n a_n written as complex128 [nmax+1].

@@ -65,55 +65,47 @@ hipError_t launch_cheb(bool fp64, int vec, int kt, bool mom, bool carry, const C
 }
 
 // ------------------------------------------------------------------ moment sums
-// One workgroup per (launch slot, level) and instance: thread t handles
-// value t % (8 Rg) (kind, column, re/im) of the per-column sums and adds the
-// records of that column's work items lane, lane + lanes, ... in eight
-// interleaved partial sums; the lanes are then added in order.
+// One workgroup per (launch slot, level), column and instance: thread t sums
+// value t % 8 ([kind][re, im]) of every 32nd of the column's records in four
+// interleaved partial sums (whole 64-byte records of neighbouring items read
+// together); the 32 lanes of a value are then added in order.  (One
+// workgroup for all columns took 32 us at 2048 records x 5 columns.)
 __global__ __launch_bounds__(256) void k_cheb_mom_finish(const MomInst* __restrict__ mi,
                                                          const double* __restrict__ partial,
-                                                         int64_t total_items, int kt, int n0,
+                                                         int64_t total_items, int n0,
                                                          int max_row) {
   __shared__ double red[256];
   const int sl = blockIdx.x;                     // slot * kt + level
   const int row = n0 + sl;                       // order produced by that level
-  const MomInst& M = mi[blockIdx.y];
-  const int nval = 8 * M.Rg;
-  const int lanes = 256 / nval;
-  const int t = threadIdx.x;
-  const int lanei = t / nval, vi = t - lanei * nval;
-  const int kindk = vi / (2 * M.Rg);
-  const int rem = vi - kindk * 2 * M.Rg;
-  const int c = rem >> 1, comp = rem & 1;
-  double s = 0.0;
-  if (lanei < lanes && row <= max_row) {
-    const int64_t ipc = M.n_tiles / M.Rg;        // work items per column
-    const double* base = partial + ((int64_t)sl * total_items + M.tile0 + c * ipc) * 8 +
-                         kindk * 2 + comp;
-    double q[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    int64_t k = lanei;
-    for (; k + 7 * lanes < ipc; k += 8 * lanes) {
+  const MomInst& M = mi[blockIdx.z];
+  const int c = blockIdx.y;
+  if (c >= M.Rg || row > max_row) return;
+  const int t = threadIdx.x, vi = t & 7, lanei = t >> 3;
+  const int64_t ipc = M.n_tiles / M.Rg;          // work items per column
+  const double* base = partial + ((int64_t)sl * total_items + M.tile0 + c * ipc) * 8 + vi;
+  double q[4] = {0, 0, 0, 0};
+  int64_t k = lanei;
+  for (; k + 3 * 32 < ipc; k += 4 * 32) {
 #pragma unroll
-      for (int u = 0; u < 8; ++u) q[u] += base[(k + u * lanes) * 8];
-    }
-    for (int u = 0; k < ipc; k += lanes, ++u) q[u & 7] += base[k * 8];
-    s = ((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7]));
+    for (int u = 0; u < 4; ++u) q[u] += base[(k + u * 32) * 8];
   }
-  red[t] = s;
+  for (int u = 0; k < ipc; k += 32, ++u) q[u] += base[k * 8];
+  red[t] = (q[0] + q[1]) + (q[2] + q[3]);
   __syncthreads();
-  if (t < nval && row <= max_row) {
+  if (t < 8) {
     double sum = 0.0;
-    for (int l = 0; l < lanes; ++l) sum += red[l * nval + t];
+    for (int l = 0; l < 32; ++l) sum += red[l * 8 + t];
     // dots row `row`, layout [kind][Rg][re, im]
-    M.dots[(int64_t)row * nval + (kindk * M.Rg + c) * 2 + comp] = sum;
+    M.dots[(int64_t)row * 8 * M.Rg + ((t >> 1) * M.Rg + c) * 2 + (t & 1)] = sum;
   }
 }
 
-hipError_t launch_cheb_mom_finish(const MomInst* d_mi, int n_inst, const double* partial,
-                                  int64_t total_items, int kt, int n_slots, int n0, int max_row,
-                                  hipStream_t s) {
+hipError_t launch_cheb_mom_finish(const MomInst* d_mi, int n_inst, int rg_max,
+                                  const double* partial, int64_t total_items, int kt, int n_slots,
+                                  int n0, int max_row, hipStream_t s) {
   if (n_slots <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_cheb_mom_finish, dim3(n_slots * kt, n_inst), dim3(256), 0, s, d_mi,
-                     partial, total_items, kt, n0, max_row);
+  hipLaunchKernelGGL(k_cheb_mom_finish, dim3(n_slots * kt, rg_max, n_inst), dim3(256), 0, s, d_mi,
+                     partial, total_items, n0, max_row);
   return hipGetLastError();
 }
 

@@ -393,34 +393,46 @@ hipError_t launch_contract_f64(const ContractInst* d_inst, const ContractArgs& a
   return hipGetLastError();
 }
 
-// Sum the workgroup partials of every column in workgroup order (FP64).
-// The block's first time index comes from t0_dev[0] when it is given (a
-// block replayed from a HIP graph), else from t0.
-__global__ void k_finish(const FinishInst* __restrict__ insts, int n_inst, int bcols,
-                         int64_t t0, const int64_t* __restrict__ t0_dev) {
-  const int ii = blockIdx.y;
-  if (ii >= n_inst) return;
-  const FinishInst& I = insts[ii];
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= bcols * I.Rg) return;
+// Sum the workgroup partials of every column (FP64): a workgroup owns 32
+// times of one column, its eight rows of threads each every eighth partial,
+// added in row order (one thread per time over all partials took 9 us with
+// 64 of them and 101 us with 683).  The block's first time index comes from
+// t0_dev[0] when it is given (a block replayed from a HIP graph), else from
+// t0.
+__global__ __launch_bounds__(256) void k_finish(const FinishInst* __restrict__ insts, int bcols,
+                                                int64_t t0, const int64_t* __restrict__ t0_dev) {
+  __shared__ double2 red[8][32];
+  const FinishInst& I = insts[blockIdx.z];
+  const int c = blockIdx.y;
+  if (c >= I.Rg) return;
   if (t0_dev) t0 = t0_dev[0];
-  const int j = e / I.Rg, c = e - j * I.Rg;
-  const double2* p = reinterpret_cast<const double2*>(I.partial);
+  const int jj = threadIdx.x & 31, row = threadIdx.x >> 5;
+  const int j = blockIdx.x * 32 + jj;
+  const double2* p = reinterpret_cast<const double2*>(I.partial) + (int64_t)c * I.wpc * bcols;
   double sx = 0.0, sy = 0.0;
-  for (int w = 0; w < I.wpc; ++w) {
-    const double2 v = p[((int64_t)c * I.wpc + w) * bcols + j];
-    sx += v.x;
-    sy += v.y;
+  if (j < bcols) {
+#pragma unroll 4
+    for (int w = row; w < I.wpc; w += 8) {
+      const double2 v = p[(int64_t)w * bcols + j];
+      sx += v.x;
+      sy += v.y;
+    }
   }
-  double2* cr = reinterpret_cast<double2*>(I.corr);
-  cr[(t0 + 1 + j) * I.ldc + I.col0 + c] = make_double2(sx, sy);
+  red[row][jj] = make_double2(sx, sy);
+  __syncthreads();
+  if (row == 0 && j < bcols) {
+    for (int q = 1; q < 8; ++q) {
+      sx += red[q][jj].x;
+      sy += red[q][jj].y;
+    }
+    reinterpret_cast<double2*>(I.corr)[(t0 + 1 + j) * I.ldc + I.col0 + c] = make_double2(sx, sy);
+  }
 }
 
-hipError_t launch_finish(const FinishInst* d_inst, int n_inst, int bcols, int64_t t0,
+hipError_t launch_finish(const FinishInst* d_inst, int n_inst, int bcols, int rg_max, int64_t t0,
                          const int64_t* t0_dev, hipStream_t s) {
-  const int need = bcols * kMaxGroupCols;
-  const dim3 grid(static_cast<unsigned>(ceil_div(need, 256)), n_inst), block(256);
-  hipLaunchKernelGGL(k_finish, grid, block, 0, s, d_inst, n_inst, bcols, t0, t0_dev);
+  const dim3 grid(static_cast<unsigned>(ceil_div(bcols, 32)), rg_max, n_inst), block(256);
+  hipLaunchKernelGGL(k_finish, grid, block, 0, s, d_inst, bcols, t0, t0_dev);
   return hipGetLastError();
 }
 

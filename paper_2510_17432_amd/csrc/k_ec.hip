@@ -199,34 +199,52 @@ __device__ inline double block_sum256(double x, double* red) {
   return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// workgroup per (c, e)
+// Workgroup of 1024 per (c, e), four orbitals a thread in flight; wave sums
+// added in order (256 threads with one orbital in flight: 245 us for 98
+// states of 131072 orbitals, latency-bound).
 template <typename T>
-__global__ __launch_bounds__(256) void k_ec_norm(int64_t N, int Rg, int nE,
-                                                 const T* __restrict__ psi,
-                                                 const T* __restrict__ qe,
-                                                 double* __restrict__ nrm, int q0) {
-  __shared__ double red[4];
+__global__ __launch_bounds__(1024) void k_ec_norm(int64_t N, int Rg, int nE,
+                                                  const T* __restrict__ psi,
+                                                  const T* __restrict__ qe,
+                                                  double* __restrict__ nrm, int q0) {
+  __shared__ double red[16][2];
   const int c = blockIdx.x / nE, e = blockIdx.x - c * nE;
   const T* p = psi + 2 * (int64_t)c * N;
   const T* q = qe + 2 * ((int64_t)e * Rg + c) * N;
   double sr = 0.0, si = 0.0;
-  for (int64_t s = threadIdx.x; s < N; s += 256) {
+#pragma unroll 4
+  for (int64_t s = threadIdx.x; s < N; s += 1024) {
     const double pr = p[2 * s], pi = p[2 * s + 1], qr = q[2 * s], qi = q[2 * s + 1];
     sr += pr * qr + pi * qi;
     si += pr * qi - pi * qr;
   }
-  sr = block_sum256(sr, red);
-  si = block_sum256(si, red);
-  if (threadIdx.x == 0) nrm[q0 + c * nE + e] = sqrt(sr * sr + si * si);
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) {
+    sr += __shfl_xor(sr, m);
+    si += __shfl_xor(si, m);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    red[threadIdx.x >> 6][0] = sr;
+    red[threadIdx.x >> 6][1] = si;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    sr = si = 0.0;
+    for (int w = 0; w < 16; ++w) {
+      sr += red[w][0];
+      si += red[w][1];
+    }
+    nrm[q0 + c * nE + e] = sqrt(sr * sr + si * si);
+  }
 }
 
 hipError_t launch_ec_norm(bool fp64, int64_t N, int Rg, int nE, const void* psi, const void* qe,
                           double* nrm, int q0, hipStream_t s) {
   if (fp64)
-    hipLaunchKernelGGL(k_ec_norm<double>, dim3(Rg * nE), dim3(256), 0, s, N, Rg, nE,
+    hipLaunchKernelGGL(k_ec_norm<double>, dim3(Rg * nE), dim3(1024), 0, s, N, Rg, nE,
                        static_cast<const double*>(psi), static_cast<const double*>(qe), nrm, q0);
   else
-    hipLaunchKernelGGL(k_ec_norm<float>, dim3(Rg * nE), dim3(256), 0, s, N, Rg, nE,
+    hipLaunchKernelGGL(k_ec_norm<float>, dim3(Rg * nE), dim3(1024), 0, s, N, Rg, nE,
                        static_cast<const float*>(psi), static_cast<const float*>(qe), nrm, q0);
   return hipGetLastError();
 }
@@ -501,26 +519,43 @@ __global__ __launch_bounds__(256) void k_ec_moments_f64(const EcInst* __restrict
   }
 }
 
-// mu[n_lo + rel][q0 + c nE + e] = sum over slices (in order), FP64
+// mu[n_lo + rel][q0 + c nE + e] = sum over slices, FP64: a workgroup owns 32
+// energies of one order and column, its eight rows of threads each every
+// eighth slice, added in row order (one thread per moment over 512 slices:
+// 114 us for a chunk of 128 orders x 98 moments).
 template <typename P>
-__global__ void k_ec_mu_finish(const EcInst* __restrict__ insts, EcArgs a) {
-  const EcInst& I = insts[blockIdx.y];
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t per = (int64_t)a.n_cnt * I.Rg * a.nE;
-  if (t >= per) return;
-  const int rel = static_cast<int>(t / ((int64_t)I.Rg * a.nE));
-  const int rest = static_cast<int>(t - (int64_t)rel * I.Rg * a.nE);
-  const int c = rest / a.nE, e = rest - c * a.nE;
-  const P* part = static_cast<const P*>(I.partial);
+__global__ __launch_bounds__(256) void k_ec_mu_finish(const EcInst* __restrict__ insts, EcArgs a) {
+  __shared__ double2 red[8][32];
+  const EcInst& I = insts[blockIdx.z];
+  const int c = blockIdx.y;
+  if (c >= I.Rg) return;
+  const int n_et = (a.nE + 31) / 32;
+  const int rel = blockIdx.x / n_et;
+  const int ee = threadIdx.x & 31, row = threadIdx.x >> 5;
+  const int e = (blockIdx.x - rel * n_et) * 32 + ee;
+  const P* part = static_cast<const P*>(I.partial) +
+                  2 * (((int64_t)c * I.n_slices * a.K + rel) * a.ldp + e);
+  const int64_t step = 2 * (int64_t)a.K * a.ldp;
   double sr = 0.0, si = 0.0;
-  for (int sl = 0; sl < I.n_slices; ++sl) {
-    const P* p = part + 2 * ((((int64_t)c * I.n_slices + sl) * a.K + rel) * a.ldp + e);
-    sr += (double)p[0];
-    si += (double)p[1];
+  if (e < a.nE) {
+#pragma unroll 4
+    for (int sl = row; sl < I.n_slices; sl += 8) {
+      const P* p = part + sl * step;
+      sr += (double)p[0];
+      si += (double)p[1];
+    }
   }
-  double* m = a.mu + 2 * ((int64_t)(a.n_lo + rel) * a.ldmu + I.q0 + c * a.nE + e);
-  m[0] = sr;
-  m[1] = si;
+  red[row][ee] = make_double2(sr, si);
+  __syncthreads();
+  if (row == 0 && e < a.nE) {
+    for (int q = 1; q < 8; ++q) {
+      sr += red[q][ee].x;
+      si += red[q][ee].y;
+    }
+    double* m = a.mu + 2 * ((int64_t)(a.n_lo + rel) * a.ldmu + I.q0 + c * a.nE + e);
+    m[0] = sr;
+    m[1] = si;
+  }
 }
 
 hipError_t launch_ec_moments(bool fp64, const EcInst* d_inst, int n_inst, const EcArgs& a,
@@ -554,8 +589,7 @@ hipError_t launch_ec_moments(bool fp64, const EcInst* d_inst, int n_inst, const 
 
 hipError_t launch_ec_mu_finish(bool fp64, const EcInst* d_inst, int n_inst, int rg_max,
                                const EcArgs& a, hipStream_t s) {
-  const int64_t per = (int64_t)a.n_cnt * rg_max * a.nE;
-  const dim3 grid((unsigned)ceil_div(per, 256), n_inst);
+  const dim3 grid((unsigned)(a.n_cnt * ceil_div(a.nE, 32)), rg_max, n_inst);
   if (fp64) hipLaunchKernelGGL(k_ec_mu_finish<double>, grid, dim3(256), 0, s, d_inst, a);
   else hipLaunchKernelGGL(k_ec_mu_finish<float>, grid, dim3(256), 0, s, d_inst, a);
   return hipGetLastError();

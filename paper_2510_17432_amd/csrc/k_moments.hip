@@ -39,27 +39,74 @@ __global__ void k_mom_assemble(const MomCorrInst* __restrict__ mc, int Nk, int h
 }
 
 // corr[(t0 + 1 + j) * ldc + col0 + r] = sum_{n <= N((j+1) tau)} (-i)^n a[j][n] mu_n[r]
-__global__ void k_mom_corr(const MomCorrInst* __restrict__ mc, const double* __restrict__ a,
-                           int lda, const int32_t* __restrict__ ntr, int bk, int64_t t0) {
+// A wave owns four times and four columns: its lanes take the orders n =
+// lane, lane + 64, ... (coalesced coefficient rows; n mod 4 is the lane's, so
+// (-i)^n is applied once at the end) and are summed by a fixed butterfly.
+// One thread per time and column over all orders, each reading its own row,
+// took 1.99 ms for 2048 times x 4 columns of up to 6547 orders.
+constexpr int kMcT = 4, kMcC = 4;
+
+__global__ __launch_bounds__(256) void k_mom_corr(const MomCorrInst* __restrict__ mc,
+                                                  const double* __restrict__ a, int lda,
+                                                  const int32_t* __restrict__ ntr, int bk,
+                                                  int64_t t0) {
   const MomCorrInst& M = mc[blockIdx.y];
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= bk * M.Rg) return;
-  const int j = e / M.Rg, r = e - j * M.Rg;
-  const double* aj = a + (int64_t)j * lda;
+  const int lane = threadIdx.x & 63;
+  const int j0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * kMcT;
+  const int r0 = blockIdx.z * kMcC;
+  const int Rg = M.Rg;
+  if (j0 >= bk || r0 >= Rg) return;
   const double2* mu = reinterpret_cast<const double2*>(M.mu);
-  double sx = 0.0, sy = 0.0;
-  const int nt = ntr[j];
-  for (int n = 0; n <= nt; ++n) {
-    const double c = aj[n];
-    const double2 m = mu[(int64_t)n * M.Rg + r];
-    switch (n & 3) {                      // (-i)^n (m.x + i m.y)
-      case 0: sx += c * m.x; sy += c * m.y; break;
-      case 1: sx += c * m.y; sy -= c * m.x; break;
-      case 2: sx -= c * m.x; sy -= c * m.y; break;
-      default: sx -= c * m.y; sy += c * m.x; break;
+  int nt[kMcT], nmax = 0;
+#pragma unroll
+  for (int q = 0; q < kMcT; ++q) {
+    nt[q] = j0 + q < bk ? ntr[j0 + q] : -1;
+    nmax = max(nmax, nt[q]);
+  }
+  double sx[kMcT][kMcC], sy[kMcT][kMcC];
+#pragma unroll
+  for (int q = 0; q < kMcT; ++q)
+#pragma unroll
+    for (int c = 0; c < kMcC; ++c) sx[q][c] = sy[q][c] = 0.0;
+#pragma unroll 2
+  for (int n = lane; n <= nmax; n += 64) {
+    double w[kMcT];
+#pragma unroll
+    for (int q = 0; q < kMcT; ++q) w[q] = n <= nt[q] ? a[(int64_t)(j0 + q) * lda + n] : 0.0;
+#pragma unroll
+    for (int c = 0; c < kMcC; ++c) {
+      const double2 m = r0 + c < Rg ? mu[(int64_t)n * Rg + r0 + c] : make_double2(0.0, 0.0);
+#pragma unroll
+      for (int q = 0; q < kMcT; ++q) {
+        sx[q][c] = fma(w[q], m.x, sx[q][c]);
+        sy[q][c] = fma(w[q], m.y, sy[q][c]);
+      }
     }
   }
-  reinterpret_cast<double2*>(M.corr)[(t0 + 1 + j) * M.ldc + M.col0 + r] = make_double2(sx, sy);
+  double2* corr = reinterpret_cast<double2*>(M.corr);
+#pragma unroll
+  for (int q = 0; q < kMcT; ++q)
+#pragma unroll
+    for (int c = 0; c < kMcC; ++c) {
+      double x = sx[q][c], y = sy[q][c];
+      switch (lane & 3) {                   // (-i)^n (x + i y)
+        case 0: break;
+        case 1: { const double u = x; x = y; y = -u; break; }
+        case 2: x = -x; y = -y; break;
+        default: { const double u = x; x = -y; y = u; break; }
+      }
+#pragma unroll
+      for (int m = 32; m >= 1; m >>= 1) {
+        x += __shfl_xor(x, m);
+        y += __shfl_xor(y, m);
+      }
+      if (lane == 0 && j0 + q < bk && r0 + c < Rg)
+        corr[(t0 + 1 + j0 + q) * M.ldc + M.col0 + r0 + c] = make_double2(x, y);
+    }
+}
+
+static dim3 mom_corr_grid(int bk, int n_inst, int rg_max) {
+  return dim3((unsigned)ceil_div(bk, 4 * kMcT), n_inst, (unsigned)ceil_div(rg_max, kMcC));
 }
 
 hipError_t launch_mom_corr(const MomCorrInst* d_mc, int n_inst, int Nk, int halving,
@@ -68,9 +115,8 @@ hipError_t launch_mom_corr(const MomCorrInst* d_mc, int n_inst, int Nk, int halv
   const int na = (Nk + 1) * rg_max;
   hipLaunchKernelGGL(k_mom_assemble, dim3((unsigned)ceil_div(na, 256), n_inst), dim3(256), 0, s,
                      d_mc, Nk, halving);
-  const int nc = bk * rg_max;
-  hipLaunchKernelGGL(k_mom_corr, dim3((unsigned)ceil_div(nc, 256), n_inst), dim3(256), 0, s,
-                     d_mc, d_a, lda, d_ntrunc, bk, t0);
+  hipLaunchKernelGGL(k_mom_corr, mom_corr_grid(bk, n_inst, rg_max), dim3(256), 0, s, d_mc, d_a,
+                     lda, d_ntrunc, bk, t0);
   return hipGetLastError();
 }
 
@@ -79,9 +125,8 @@ hipError_t launch_mom_corr(const MomCorrInst* d_mc, int n_inst, int Nk, int halv
 hipError_t launch_mom_corr_only(const MomCorrInst* d_mc, int n_inst, const double* d_a, int lda,
                                 const int32_t* d_ntrunc, int bk, int64_t t0, int rg_max,
                                 hipStream_t s) {
-  const int64_t nc = (int64_t)bk * rg_max;
-  hipLaunchKernelGGL(k_mom_corr, dim3((unsigned)ceil_div(nc, 256), n_inst), dim3(256), 0, s,
-                     d_mc, d_a, lda, d_ntrunc, bk, t0);
+  hipLaunchKernelGGL(k_mom_corr, mom_corr_grid(bk, n_inst, rg_max), dim3(256), 0, s, d_mc, d_a,
+                     lda, d_ntrunc, bk, t0);
   return hipGetLastError();
 }
 
