@@ -113,11 +113,9 @@ __device__ __forceinline__ void stv(CSP_GLOBAL float* p, const cx<float> (&d)[V]
     q[k] = t;
   }
 }
-// Chebyshev vectors are written once and read back only after many other
-// vectors have streamed through the caches: non-temporal stores.
-#ifndef CSP_CHEB_NT
-#define CSP_CHEB_NT 1
-#endif
+// The orders of a state form are written once and read back only after many
+// other vectors have streamed through the caches: non-temporal stores.  The
+// moment forms write the two vectors that the next launch reads: cached.
 template <int V>
 __device__ __forceinline__ void stv_nt(CSP_GLOBAL float* p, const cx<float> (&d)[V]) {
   CSP_GLOBAL f32x4u* q = reinterpret_cast<CSP_GLOBAL f32x4u*>(p);
@@ -128,11 +126,7 @@ __device__ __forceinline__ void stv_nt(CSP_GLOBAL float* p, const cx<float> (&d)
     t.y = d[2 * k].y;
     t.z = d[2 * k + 1].x;
     t.w = d[2 * k + 1].y;
-#if CSP_CHEB_NT
     __builtin_nontemporal_store(t, q + k);
-#else
-    q[k] = t;
-#endif
   }
 }
 template <int V>
@@ -163,11 +157,7 @@ __device__ __forceinline__ void stv_nt(CSP_GLOBAL double* p, const cx<double> (&
     f64x2u t;
     t.x = d[v].x;
     t.y = d[v].y;
-#if CSP_CHEB_NT
     __builtin_nontemporal_store(t, q + v);
-#else
-    q[v] = t;
-#endif
   }
 }
 __device__ __forceinline__ cx<float> ld1(const CSP_GLOBAL float* p) {
@@ -354,9 +344,12 @@ __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts
   const int64_t item = item_lo + xcd_remap(blockIdx.x, gridDim.x) * 4 + wave;
   if (item >= item_hi) return;                     // a whole wave; no barriers below
   // the last instance whose first item is not past this one: 64 at a time
-  int ii = -1;
-  for (int k = 0; k < n_inst; k += 64)
-    ii += __popcll(__ballot(k + lane < n_inst && item >= insts[k + lane].item0));
+  int ii = 0;
+  if (n_inst > 1) {
+    ii = -1;
+    for (int k = 0; k < n_inst; k += 64)
+      ii += __popcll(__ballot(k + lane < n_inst && item >= insts[k + lane].item0));
+  }
   const ChebInst& I = insts[ii];
 
   // ---- geometry of this work item (wave-uniform)
@@ -844,8 +837,9 @@ __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts
               if (l > lmax) break;
               if (!owned_row(i - nlev - l) || (MOM != kMomNone && l < nlev - 1)) continue;
             }
-            if (l < KT) stv_nt<V>((gT*)(outb[l - 1] + so), rr[l < KT ? l : 0][SHI]);
-            else stv_nt<V>((gT*)(outb[l - 1] + so), olast);
+            const C(&row)[V] = l < KT ? rr[l < KT ? l : 0][SHI] : olast;
+            if constexpr (MOM == kMomNone) stv_nt<V>((gT*)(outb[l - 1] + so), row);
+            else stv<V>((gT*)(outb[l - 1] + so), row);
           }
         }
         so += static_cast<unsigned>(pitchB);
