@@ -581,17 +581,43 @@ struct ChebPlan {
   std::vector<ChebRun> runs;   // one launch per run of same-class instances
 };
 
+// Rows per work item of a kernel that keeps one wave on a SIMD (the
+// sequential form: seven complex128 steps in registers): a launch lasts
+// (waves / SIMDs, rounded up) rounds of (rows + 2 kt margin rows + a fixed
+// part worth about 7 rows).  Graphene 1024^2 x 4 columns in 2432 waves of 32
+// rows takes three rounds (220 us), in 988 of 79 rows one (171 us).
+int round_rows(const std::vector<ChebInst>& insts, int ow, int kt, int n_cu) {
+  int64_t ly = 1;
+  for (auto& I : insts) ly = std::max(ly, I.Ly);
+  int64_t best_rows = 64, last = 0;
+  double best = 1e300;
+  for (int64_t k = 1; k <= ly; ++k) {
+    const int64_t rows = ceil_div(ly, k);
+    if (rows == last || rows > 128) continue;
+    if (rows < 4 && ly >= 4) break;
+    last = rows;
+    int64_t n = 0;
+    for (auto& I : insts) n += I.Rg * ceil_div(I.opr, ow) * ceil_div(I.Ly, rows);
+    const double t = (double)(rows + 2 * kt + 7) * (double)ceil_div(n, (int64_t)n_cu * 4);
+    if (t < best * 0.999) {
+      best = t;
+      best_rows = rows;
+    }
+  }
+  return (int)best_rows;
+}
+
 // Work items (waves) of the instances for strips of 64 vec values carrying
 // kt levels, and segments of seg_rows rows; 0 arguments choose defaults
 // (the autotuner passes what it measured).
 ChebPlan plan_cheb(std::vector<ChebInst>& insts, bool fp64, bool mom, int n_cu, int vec = 0,
-                   int kt = 0, int seg = 0) {
+                   int kt = 0, int seg = 0, bool seq = false) {
   ChebPlan p;
   p.vec = vec > 0 ? vec : 2;
   p.kt = kt > 0 ? kt : 1;
   for (auto& I : insts)
     if (I.kind == CSP_SPARSE) p.kt = 1;   // explicit matrices: one step per launch
-  if (!cheb_shape_supported(fp64, p.vec, p.kt, mom)) {
+  if (!seq && !cheb_shape_supported(fp64, p.vec, p.kt, mom)) {
     p.vec = 2;
     p.kt = 1;
   }
@@ -601,10 +627,15 @@ ChebPlan plan_cheb(std::vector<ChebInst>& insts, bool fp64, bool mom, int n_cu, 
     if (I.kind != CSP_SPARSE) items_rows1 += I.Rg * ceil_div(I.opr, p.ow) * I.Ly;
   if (seg > 0) {
     p.seg_rows = seg;
+  } else if (seq) {
+    p.seg_rows = round_rows(insts, p.ow, p.kt, n_cu);
   } else {
-    // long segments amortise the 2 kt margin rows; keep >= 8 waves per CU
+    // long segments amortise the 2 kt margin rows; keep >= 8 waves per CU,
+    // down to 4 rows (2 in the state forms, whose results do not depend on
+    // the segments as the FP32 moment sums do: 64 x 64 sites 14 -> 12 us)
     p.seg_rows = 64;
-    while (p.seg_rows > 4 && items_rows1 / p.seg_rows < (int64_t)n_cu * 8) p.seg_rows /= 2;
+    while (p.seg_rows > (mom ? 4 : 2) && items_rows1 / p.seg_rows < (int64_t)n_cu * 8)
+      p.seg_rows /= 2;
   }
   // explicit matrices: a wave owns 128 rows of ell_ct columns; items are
   // the moment records, one per (column, 128-row chunk)
@@ -1004,6 +1035,8 @@ extern "C" csp_status csp_propagate_batch(csp_context* c, int32_t n_inst,
 
 static csp_status propagate_moments_impl(csp_context* c, const std::vector<InstIn>& ins,
                                          const csp_params& P, double t_start, csp_report* rep);
+static csp_status propagate_seq_impl(csp_context* c, const std::vector<InstIn>& ins,
+                                     const csp_params& P, double t_start, csp_report* rep);
 
 // Column windows.  Every column is propagated independently, so when even
 // the smallest workspace (a 16-order chunk plus psi0 and carry for the
@@ -1102,6 +1135,15 @@ static csp_status propagate_impl(csp_context* c, const std::vector<InstIn>& ins,
     }
   }
   if (P.assembly == CSP_ASSEMBLE_MOMENTS) return propagate_moments_impl(c, ins, P, t_start, rep);
+  // The sequential form of stencil lattices accumulates the carried state in
+  // the recursion.  Explicit matrices (one step per launch: the carried state
+  // would be read and written at every step, two vectors against one) and
+  // calls that replay a graph keep the ring and the contraction.
+  if (P.mode == CSP_FP64_SEQ && !(P.graph > 0 || (P.graph == 0 && ins.size() > 1 && batch_call))) {
+    bool stencil = true;
+    for (auto& in : ins) stencil = stencil && in.lat->g.kind != CSP_SPARSE;
+    if (stencil) return propagate_seq_impl(c, ins, P, t_start, rep);
+  }
   const bool fp64 = P.mode != CSP_FP32_CONC;
   const size_t csz = fp64 ? sizeof(double2) : sizeof(float2);
   for (size_t i = 0; i < ins.size(); ++i) {
@@ -1576,6 +1618,11 @@ static csp_status propagate_moments_impl(csp_context* c, const std::vector<InstI
   const bool single = b >= Nt;
   const bool halving = single && !want_final && Nt > 0;
   const bool carry = !single || want_final;
+  // complex128: mu_0 and mu_1 from <psi0|psi0> and <phi_1|phi_0> too, so no
+  // launch of a stencil lattice reads psi0 (in complex64 the first launch
+  // sums both against psi0)
+  bool self_first = halving && fp64;
+  for (auto& in : ins) self_first = self_first && in.lat->g.kind != CSP_SPARSE;
   const int64_t b_last = Nt > 0 ? Nt - (ceil_div(Nt, b) - 1) * b : b;
 
   // Coefficient table a[j][n], x = (j + 1) tau, j < b.
@@ -1638,7 +1685,7 @@ static csp_status propagate_moments_impl(csp_context* c, const std::vector<InstI
   int vec_want = tune ? tune->spmm_vec : 0;
   // default: 8 steps per launch for the complex64 self-product kernel
   // (halving), 4 where psi0 or the carried state take registers
-  int kt_want = tune ? tune->spmm_steps : (halving && !fp64 ? 8 : 4);
+  int kt_want = tune ? tune->spmm_steps : (halving ? 8 : 4);
   if (carry && !cheb_carry_supported(fp64, 2, kt_want)) kt_want = 4;
   if (carry) vec_want = 2;   // the carried-state kernels hold 2 values per lane
   const ChebPlan sp_plan = plan_cheb(sp, fp64, true, c->n_cu, vec_want, kt_want,
@@ -1786,7 +1833,7 @@ static csp_status propagate_moments_impl(csp_context* c, const std::vector<InstI
       // <phi_k|phi_k> and <phi_k|phi_k-1> (Eq. cheby_prod): psi0 is read by
       // the first launch only (mu_0, mu_1); the others run the kernel
       // without psi0.
-      st.dot_psi0 = (!halving || produced == 0) ? 1 : 0;
+      st.dot_psi0 = (!halving || (produced == 0 && !self_first)) ? 1 : 0;
       st.dot_self = halving ? 1 : 0;
       st.mom_slot = launches;
       st.partial = d_part;
@@ -1828,8 +1875,8 @@ static csp_status propagate_moments_impl(csp_context* c, const std::vector<InstI
       }
     }
     ndot += Nk;
-    HIPCALL(launch_mom_corr(d_mc, (int)mc.size(), Nk, halving ? 1 : 0, d_a, lda, d_ntr, bk, t0,
-                            rmax, s));
+    HIPCALL(launch_mom_corr(d_mc, (int)mc.size(), Nk, halving ? (self_first ? 2 : 1) : 0, d_a, lda,
+                            d_ntr, bk, t0, rmax, s));
     if (P.check_norm) {
       for (size_t gi = 0; gi < groups.size(); ++gi) {
         const Group& g = groups[gi];
@@ -1868,6 +1915,247 @@ static csp_status propagate_moments_impl(csp_context* c, const std::vector<InstI
     rep->ms_spmm = ms_s;
     rep->ms_contract = ms_c;
     rep->spmm_bytes = spmm_bytes;
+    rep->contract_bytes = 0;
+    rep->contract_flops = 0;
+    rep->workspace_bytes = c->ws_size;
+    rep->graph_blocks = 0;
+    rep->n_passes = 1;
+    rep->spmm_steps = kt;
+  }
+  return CSP_OK;
+}
+
+// ------------------------------------------------------------------ sequential form
+// Sequential propagation (Sec. II.A), complex128: every time step is one
+// Chebyshev expansion of order N(tau~) of the state before it.  The
+// recursion's epilogue adds c_n phi_n to the next state as the orders are
+// produced, and the step's last launch also sums <psi0|psi(t_j)>, so the
+// orders are never stored beyond the two that a launch hands to the next:
+// with 20 orders and five steps per launch 21 vectors move per time step,
+// against 51 with a ring of orders and a contraction.
+static csp_status propagate_seq_impl(csp_context* c, const std::vector<InstIn>& ins,
+                                     const csp_params& P, double t_start, csp_report* rep) {
+  for (size_t i = 0; i < ins.size(); ++i)
+    if (ins[i].lat->ctx->device != c->device)
+      return fail(CSP_EINVAL, "instance %zu: lattice on another device", i);
+  DeviceGuard dg(c->device);
+  hipStream_t s = c->stream;
+  const size_t csz = sizeof(double2);
+  const int64_t Nt = P.Nt;
+
+  // Coefficients a_n(tau~) of one step.
+  const int nmax = (int)trunc_nmax(P.tau_tilde);
+  struct Free {
+    std::vector<void*> p;
+    ~Free() { for (void* q : p) (void)hipFree(q); }
+  } tmp;
+  double* d_a = nullptr;
+  int32_t* d_ntr = nullptr;
+  HIPCALL(hipMalloc(&d_a, sizeof(double) * (nmax + 1)));
+  tmp.p.push_back(d_a);
+  HIPCALL(hipMalloc(&d_ntr, sizeof(int32_t)));
+  tmp.p.push_back(d_ntr);
+  HIPCALL(launch_bessel(P.tau_tilde, 1, nmax, P.eta, true, d_a, d_ntr, s));
+  std::vector<double> a(nmax + 1);
+  int32_t Nk = 0;
+  HIPCALL(hipMemcpyAsync(a.data(), d_a, sizeof(double) * (nmax + 1), hipMemcpyDeviceToHost, s));
+  HIPCALL(hipMemcpyAsync(&Nk, d_ntr, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+  HIPCALL(hipStreamSynchronize(s));
+  if (Nk < 1) return fail(CSP_ENUMERIC, "no truncation order for x = %g", P.tau_tilde);
+
+  std::vector<Group> groups;
+  int64_t vec_alg = 0;
+  int rmax = 1;
+  for (size_t i = 0; i < ins.size(); ++i) {
+    int col = ins[i].col_base;
+    for (int Rg : split_columns(ins[i].R)) {
+      Group g;
+      g.inst = (int)i;
+      g.col0 = col;
+      g.Rg = Rg;
+      set_layout(g, ins[i].lat);
+      groups.push_back(g);
+      vec_alg += ins[i].lat->g.N * Rg;
+      rmax = std::max(rmax, Rg);
+      col += Rg;
+    }
+  }
+  std::vector<ChebInst> sp;
+  for (auto& g : groups) {
+    sp.push_back(make_inst(ins[g.inst].lat, g.Rg, true));
+    apply_layout(sp.back(), g);
+  }
+  const csp_tuning* tune = find_tuning(c, ins, true, CSP_ASSEMBLE_STATES);
+  const int kt = kSeqSteps;
+  const ChebPlan plan = plan_cheb(sp, true, false, c->n_cu, 2, kt, tune ? tune->spmm_seg_rows : 0,
+                                  true);
+  constexpr int kRecSlots = 16;      // time steps whose records wait for one sum
+
+  // Workspace: four slots, psi0 and two carried states per group.
+  const size_t n_sd = 256;
+  const size_t rec_bytes = (size_t)kRecSlots * plan.total_items * sizeof(double2);
+  size_t need = align256(rec_bytes) + align256(sizeof(double) * n_sd * kMaxGroupCols) +
+                align256(2 * sizeof(int)) + 2 * align256(sizeof(ChebInst) * groups.size()) +
+                align256(sizeof(SeqInst) * groups.size());
+  for (auto& g : groups) need += align256(4 * g.stride() * csz) + 3 * align256(g.M * csz);
+  size_t cap = 0;
+  CHECK(memory_cap(c, P.mem_cap_bytes, &cap));
+  if (need > cap)
+    return fail(CSP_ENOMEM, "workspace %.2f GB exceeds the cap %.2f GB", need / 1e9, cap / 1e9);
+  CHECK(ws_reserve(c, need));
+  Carver cv(c->ws);
+  double* d_rec = (double*)cv.take(rec_bytes);
+  double* d_sd = (double*)cv.take(sizeof(double) * n_sd * kMaxGroupCols);
+  int* d_flag = (int*)cv.take(2 * sizeof(int));
+  // two instance tables: the carried state alternates between two buffers
+  ChebInst* d_inst[2];
+  for (auto& d : d_inst) d = (ChebInst*)cv.take(sizeof(ChebInst) * groups.size());
+  SeqInst* d_si = (SeqInst*)cv.take(sizeof(SeqInst) * groups.size());
+  std::vector<void*> state[2];
+  std::vector<SeqInst> si;
+  for (size_t gi = 0; gi < groups.size(); ++gi) {
+    Group& g = groups[gi];
+    const InstIn& in = ins[g.inst];
+    g.slots = cv.take(4 * g.stride() * csz);
+    g.psi0g = cv.take(g.M * csz);
+    for (auto& v : state) v.push_back(cv.take(g.M * csz));
+    // the recursion writes rows only; the norm guard reads whole vectors
+    if (g.pitch > 0)
+      HIPCALL(launch_zero_pad(state[1][gi], 1, 0, g.Rg, g.cstride, in.lat->g.Ly, in.lat->g.opr,
+                              g.pitch, true, s));
+    HIPCALL(launch_gather_cols(in.lat->g.N, in.ld, g.col0, g.Rg, CSP_C128, in.psi0, true, g.psi0g,
+                               s, in.lat->g.opr, g.pitch));
+    HIPCALL(launch_self_dot(g.cstride, g.Rg, g.psi0g, true, in.corr, g.col0, d_sd, (int)n_sd, s));
+    HIPCALL(hipMemcpyAsync(state[0][gi], g.psi0g, g.M * csz, hipMemcpyDeviceToDevice, s));
+    sp[gi].base = g.slots;
+    sp[gi].slot_stride = g.stride();
+    sp[gi].psi0 = g.psi0g;
+    SeqInst q{};
+    q.item0 = sp[gi].item0;
+    q.items_per_col = sp[gi].n_strips * sp[gi].n_segs;
+    q.corr = in.corr;
+    q.ldc = in.ld;
+    q.Rg = g.Rg;
+    q.col0 = g.col0;
+    si.push_back(q);
+  }
+  std::vector<ChebInst> tab[2] = {sp, sp};
+  for (int k = 0; k < 2; ++k) {
+    for (size_t gi = 0; gi < groups.size(); ++gi) {
+      tab[k][gi].src = state[k][gi];
+      tab[k][gi].carry = state[1 - k][gi];
+    }
+    HIPCALL(hipMemcpyAsync(d_inst[k], tab[k].data(), sizeof(ChebInst) * sp.size(),
+                           hipMemcpyHostToDevice, s));
+  }
+  HIPCALL(hipMemcpyAsync(d_si, si.data(), sizeof(SeqInst) * si.size(), hipMemcpyHostToDevice, s));
+  if (P.check_norm) CHECK(guard_reset(d_flag, s));
+
+  // The launches of one time step: levels as even as possible.
+  const int n_launch = (int)ceil_div(Nk, kt);
+  auto coef = [&](int n, double* out2) {
+    const double v = a[n];
+    switch (n & 3) {   // (-i)^n v
+      case 0: out2[0] = v; out2[1] = 0.0; break;
+      case 1: out2[0] = 0.0; out2[1] = -v; break;
+      case 2: out2[0] = -v; out2[1] = 0.0; break;
+      default: out2[0] = 0.0; out2[1] = v; break;
+    }
+  };
+  double eps_bytes = 0;
+  for (auto& g : groups) eps_bytes += static_bytes(ins[g.inst].lat, true);
+  const double vbytes = (double)vec_alg * csz;
+  std::vector<ChebStep> steps;
+  double step_bytes = 0.0;
+  {
+    int produced = 0, cur = -1, prev = -1;
+    for (int k = 0; k < n_launch; ++k) {
+      ChebStep st = step_args(plan);
+      st.nlev = (Nk - produced + n_launch - k - 1) / (n_launch - k);
+      const bool last = k + 1 == n_launch;
+      int fr[4], nf = 0;
+      for (int q = 0; q < 4; ++q)
+        if (q != cur && q != prev) fr[nf++] = q;
+      const int new_cur = fr[0];
+      int new_prev = fr[1];
+      if (k == 0) {
+        st.first = 1;
+        st.slot_cur = -1;
+        if (st.nlev == 1 && !last) st.copy_slot = new_prev;   // phi_0 is the next phi_{n-1}
+      } else {
+        st.slot_cur = cur;
+        st.slot_prev = prev;
+        if (st.nlev == 1) new_prev = cur;
+      }
+      if (!last) {                                  // the last launch's orders are not read again
+        st.slot_out[st.nlev - 1] = new_cur;
+        if (st.nlev >= 2) st.slot_out[st.nlev - 2] = new_prev;
+      }
+      st.carry_mode = k == 0 ? 1 : 2;
+      coef(0, st.cc0);
+      for (int l = 1; l <= st.nlev; ++l) coef(produced + l, st.ccl[l - 1]);
+      st.dot_psi0 = last ? 1 : 0;
+      st.partial = d_rec;
+      step_bytes += vbytes * ((k == 0 ? 1.0 : 2.0) + (last ? 1.0 : std::min(st.nlev, 2)) +
+                              (st.copy_slot >= 0 ? 1.0 : 0.0) + (k == 0 ? 1.0 : 2.0)) +
+                    eps_bytes;
+      produced += st.nlev;
+      cur = new_cur;
+      prev = new_prev;
+      steps.push_back(st);
+    }
+  }
+
+  Profiler prof{c, P.profile != 0};
+  int slots = 0;
+  for (int64_t j = 0; j < Nt; ++j) {
+    for (auto& st : steps) {
+      st.mom_slot = slots;
+      size_t ev = 0;
+      CHECK(prof.begin(0, &ev));
+      HIPCALL(launch_cheb(true, 2, kt, false, true, d_inst[j & 1], plan.runs, st, s));
+      CHECK(prof.end(ev));
+    }
+    ++slots;
+    if (slots == kRecSlots || j + 1 == Nt || P.check_norm) {
+      HIPCALL(launch_seq_corr(d_si, (int)si.size(), rmax, slots, d_rec, plan.total_items,
+                              j + 1 - slots, s));
+      slots = 0;
+    }
+    if (P.check_norm) {
+      for (size_t gi = 0; gi < groups.size(); ++gi) {
+        const Group& g = groups[gi];
+        const InstIn& in = ins[g.inst];
+        HIPCALL(launch_guard(g.cstride, g.Rg, state[1 - (j & 1)][gi], true, in.corr, in.ld, g.col0,
+                             j, 1, P.norm_tol, (int)j, nullptr, d_flag, d_sd, (int)n_sd, s));
+      }
+    }
+  }
+  for (size_t gi = 0; gi < groups.size(); ++gi) {
+    const Group& g = groups[gi];
+    const InstIn& in = ins[g.inst];
+    if (!in.final_out) continue;
+    HIPCALL(launch_scatter_cols(in.lat->g.N, in.ld, g.col0, g.Rg, CSP_C128, state[Nt & 1][gi], true,
+                                in.final_out, s, in.lat->g.opr, g.pitch));
+  }
+  HIPCALL(hipStreamSynchronize(s));
+  if (P.check_norm) CHECK(guard_check(d_flag, s));
+  if (rep) {
+    double ms_s = 0, ms_c = 0;
+    CHECK(prof.collect(&ms_s, &ms_c));
+    rep->block_b = 1;
+    rep->chunk_K = Nk + 1;
+    rep->n_blocks = (int)Nt;
+    rep->n_groups = (int)groups.size();
+    rep->amxsy = Nt * Nk;
+    rep->axpy = Nt * Nk;
+    rep->dot = Nt;
+    rep->spmm_launches = Nt * n_launch;
+    rep->contract_launches = 0;
+    rep->ms_total = now_ms() - t_start;
+    rep->ms_spmm = ms_s;
+    rep->ms_contract = ms_c;
+    rep->spmm_bytes = (double)Nt * step_bytes;
     rep->contract_bytes = 0;
     rep->contract_flops = 0;
     rep->workspace_bytes = c->ws_size;
@@ -2774,6 +3062,7 @@ extern "C" csp_status csp_autotune(csp_context* c, int32_t n_inst, const csp_lat
   for (int v = 2; v <= (any_sparse ? 2 : 4); v *= 2)
     for (int kt = 1; kt <= (any_sparse ? 1 : 8); kt *= 2) {
       if (!cheb_shape_supported(fp64, v, kt, mom)) continue;
+      if (fp64 && mom && kt == 8 && !halving_t) continue;   // self products only
       for (int seg = 8; seg <= (any_sparse ? 8 : 128); seg *= 2) {
         std::vector<ChebInst> tmp_sp = sp;
         ChebPlan p = plan_cheb(tmp_sp, fp64, mom, c->n_cu, v, kt, seg);

@@ -18,6 +18,7 @@ constexpr int kMaxStepCols = 64;      // columns accepted by the single-step API
 constexpr int kContractThreads = 256; // contraction workgroup (4 waves)
 constexpr int kMaxJTiles = 2;         // 32-wide time tiles: b <= 64 on MFMA
 constexpr int kMaxFp64B = 16;         // b limit of the FP64 contraction
+constexpr int kSeqSteps = 7;          // steps per launch of the sequential form
 
 // ------------------------------------------------------------------ generator
 // SplitMix64 (Steele, Lea & Flood, OOPSLA 2014).  The generator's state
@@ -173,7 +174,8 @@ struct ChebRun {
   bool win;                    // explicit matrix in the windowed layout
   int64_t win_cap;             // windowed: LDS complex values of the run's largest tile
 };
-// mom: moment epilogue; carry: also the carried state (moment epilogue only)
+// mom: moment epilogue; carry: the carried state (with moments, or alone: the
+// sequential form, complex128, kSeqSteps per launch, <psi0|carry> with dot_psi0)
 hipError_t launch_cheb(bool fp64, int vec, int kt, bool mom, bool carry, const ChebInst* d_inst,
                        const std::vector<ChebRun>& runs, const ChebStep& st, hipStream_t s);
 // Explicit (ELL) matrices: one Chebyshev step per launch, 64 rows of one
@@ -212,6 +214,16 @@ bool build_ell_windows(int64_t N, int D, const int32_t* col, const double* val, 
 // max_s sum_k |val_sk| (k in order, FP64): one maximum per block into partial
 hipError_t launch_ell_gershgorin(int64_t N, int D, const double* d_val, double* d_partial,
                                  int n_partial, hipStream_t s);
+// Sequential form: correlations from the records that a time step's last
+// launch writes (mom_slot s: records [s][item] of <psi0|carried state>).
+struct SeqInst {
+  int64_t item0, items_per_col;
+  double* corr;
+  int64_t ldc;
+  int32_t Rg, col0;
+};
+hipError_t launch_seq_corr(const SeqInst* d_si, int n_inst, int rg_max, int n_slots,
+                           const double* partial, int64_t total_items, int64_t j0, hipStream_t s);
 // (values per lane, steps per launch) pairs with a compiled kernel
 bool cheb_shape_supported(bool fp64, int vec, int kt, bool mom);
 bool cheb_carry_supported(bool fp64, int vec, int kt);

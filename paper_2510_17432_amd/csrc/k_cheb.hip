@@ -17,10 +17,12 @@ CSP_CHEB_LAUNCHER(launch_cheb_f32mc)
 CSP_CHEB_LAUNCHER(launch_cheb_f64mc)
 CSP_CHEB_LAUNCHER(launch_cheb_f32s)
 CSP_CHEB_LAUNCHER(launch_cheb_f64s)
+CSP_CHEB_LAUNCHER(launch_cheb_f64q)
 #undef CSP_CHEB_LAUNCHER
 
 bool cheb_shape_supported(bool fp64, int vec, int kt, bool mom) {
-  if (fp64) return vec == 2 && (kt == 1 || kt == 2 || kt == 4);
+  // complex128: 8 steps per launch for the self products (one block) only
+  if (fp64) return vec == 2 && (kt == 1 || kt == 2 || kt == 4 || (kt == 8 && mom));
   if (vec != 2 && vec != 4) return false;
   return kt == 1 || kt == 2 || kt == 4 || (kt == 8 && (!mom || vec == 2));
 }
@@ -34,8 +36,11 @@ int cheb_margin(int vec, int kt) { return (kt + vec - 1) / vec * vec; }
 hipError_t launch_cheb(bool fp64, int vec, int kt, bool mom, bool carry, const ChebInst* d_inst,
                        const std::vector<ChebRun>& runs, const ChebStep& st, hipStream_t s) {
   if (st.nlev < 1 || st.nlev > kt) return hipErrorInvalidValue;
-  if (!cheb_shape_supported(fp64, vec, kt, mom)) return hipErrorInvalidValue;
-  if (carry && (!mom || !cheb_carry_supported(fp64, vec, kt))) return hipErrorInvalidValue;
+  // the carried state without moments: the sequential form's kernel
+  const bool seq = carry && !mom;
+  if (seq ? !fp64 || vec != 2 || kt != kSeqSteps : !cheb_shape_supported(fp64, vec, kt, mom))
+    return hipErrorInvalidValue;
+  if (carry && mom && !cheb_carry_supported(fp64, vec, kt)) return hipErrorInvalidValue;
   // only the self products (one block, bra = ket): the kernel without psi0
   const bool self = mom && !carry && !st.dot_psi0 && st.dot_self;
   if (st.ow != 64 * vec - 2 * cheb_margin(vec, kt)) return hipErrorInvalidValue;
@@ -43,7 +48,10 @@ hipError_t launch_cheb(bool fp64, int vec, int kt, bool mom, bool carry, const C
     const ChebInst* di = d_inst + r.inst0;
     const int64_t lo = r.item0, hi = r.item0 + r.n_items;
     hipError_t e;
-    if (r.sparse && r.win)
+    if (seq)
+      e = r.sparse ? hipErrorInvalidValue
+                   : launch_cheb_f64q(vec, kt, r.honey, r.diag, di, r.n_inst, lo, hi, st, s);
+    else if (r.sparse && r.win)
       e = launch_cheb_ellw(fp64, mom, carry, r.ct, r.win_cap, di, r.n_inst, r.wave0,
                            r.wave0 + r.n_waves, st, s);
     else if (r.sparse)
@@ -62,6 +70,46 @@ hipError_t launch_cheb(bool fp64, int vec, int kt, bool mom, bool carry, const C
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+// ------------------------------------------------------------------ sequential form
+// <psi0|psi(t_{j0+1+slot})> of every column from the records of its work
+// items ([slot][item] complex): thread t adds every 256th record, the 256
+// partial sums in a fixed tree.
+__global__ __launch_bounds__(256) void k_seq_corr(const SeqInst* __restrict__ si,
+                                                  const double* __restrict__ partial,
+                                                  int64_t total_items, int64_t j0) {
+  __shared__ double2 red[256];
+  const SeqInst& I = si[blockIdx.z];
+  const int c = blockIdx.y, slot = blockIdx.x, t = threadIdx.x;
+  if (c >= I.Rg) return;
+  const double2* p = reinterpret_cast<const double2*>(partial) + (int64_t)slot * total_items +
+                     I.item0 + c * I.items_per_col;
+  double sx = 0.0, sy = 0.0;
+  for (int64_t k = t; k < I.items_per_col; k += 256) {
+    const double2 v = p[k];
+    sx += v.x;
+    sy += v.y;
+  }
+  red[t] = make_double2(sx, sy);
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if (t < w) {
+      red[t].x += red[t + w].x;
+      red[t].y += red[t + w].y;
+    }
+    __syncthreads();
+  }
+  if (t == 0)
+    reinterpret_cast<double2*>(I.corr)[(j0 + 1 + slot) * I.ldc + I.col0 + c] = red[0];
+}
+
+hipError_t launch_seq_corr(const SeqInst* d_si, int n_inst, int rg_max, int n_slots,
+                           const double* partial, int64_t total_items, int64_t j0, hipStream_t s) {
+  if (n_slots <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_seq_corr, dim3(n_slots, rg_max, n_inst), dim3(256), 0, s, d_si, partial,
+                     total_items, j0);
+  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ moment sums

@@ -333,7 +333,12 @@ template <typename T, int V, int KT, bool HONEY, bool DIAG, int MOM, bool CARRY>
 __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts, int n_inst,
                                               int64_t item_lo, int64_t item_hi, ChebStep st) {
   static_assert(V % 2 == 0, "lanes hold whole (even, odd) orbital pairs");
-  static_assert(!CARRY || MOM == kMomBra, "the carried state comes with the bra moments");
+  static_assert(!CARRY || MOM != kMomSelf, "one block with bra = ket carries no state");
+  // sequential form: the recursion with the carried state and, in a time
+  // step's last launch, <psi0|carried state>, without moments
+  constexpr bool SEQ = CARRY && MOM == kMomNone;
+  // forms that keep the two newest levels of a launch only
+  constexpr bool KEEP2 = CARRY || MOM != kMomNone;
   using C = cx<T>;
   using gT = CSP_GLOBAL T;
   using gB = CSP_GLOBAL char;
@@ -456,6 +461,8 @@ __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts
     for (int v = 0; v < V; ++v) pq[k][v] = {T(0), T(0)};
   const bool dots = MOM == kMomSelf || (MOM == kMomBra && (st.dot_psi0 || st.dot_self));
   const bool want_psi0 = MOM == kMomBra && st.dot_psi0;
+  const bool dot_carry = SEQ && st.dot_psi0;
+  T sd[2] = {T(0), T(0)};                            // <psi0|carried state> of this lane
   // carried state: partial sums of rows r0 - 1 - j (j < KT) in registers;
   // a row is read (carry_mode 2), completed and written once per launch
   const bool carry_on = CARRY && carry && st.carry_mode != 0;
@@ -478,7 +485,7 @@ __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts
   // an iteration takes less time than a load from HBM, so the plain and
   // self-product forms keep three rows in flight, one per phase; the forms
   // that also read psi0 or the carried state, one.
-  constexpr int PF = MOM == kMomBra ? 1 : 3;
+  constexpr int PF = MOM == kMomBra || CARRY || (MOM == kMomSelf && sizeof(T) == 8) ? 1 : 3;
 
   auto run = [&](auto whole_tag) {
     constexpr bool WHOLE = decltype(whole_tag)::value;
@@ -536,6 +543,7 @@ __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts
     unsigned so = lb;                                // lb + i pitchB
 
     C nc[PF][V], np[PF][V], nq[MOM == kMomBra ? PF : 1][V], nk[CARRY ? PF : 1][V];
+    C nd[SEQ ? PF : 1][V], cd[V];                    // psi0 rows of the completed carried rows
     T ne[DIAG ? PF : 1][V];
     C pv[V], car[V];
 #pragma unroll
@@ -585,6 +593,8 @@ __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts
         if (want_psi0) load_row(psi0 + lo, rp, nq[B]);
       if constexpr (CARRY) {
         if (carry_in) load_row(carry + ko, WHOLE || row_in(krow), nk[B]);
+        if constexpr (SEQ)
+          if (dot_carry) load_row(psi0 + ko, WHOLE || row_in(krow), nd[B]);
         ++krow;
         ko += pitchB;
         if (py && krow == Ly) {
@@ -643,7 +653,10 @@ __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts
       }
       if constexpr (CARRY) {
 #pragma unroll
-        for (int v = 0; v < V; ++v) car[v] = nk[B][v];
+        for (int v = 0; v < V; ++v) {
+          car[v] = nk[B][v];
+          if constexpr (SEQ) cd[v] = nd[B][v];
+        }
 #pragma unroll
         for (int k = KT - 1; k >= 1; --k)
 #pragma unroll
@@ -737,7 +750,8 @@ __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts
         }
         if (STEADY || owned_row(i - nlev - l)) {
           if constexpr (!WHOLE)
-            if (MOM == kMomNone || l >= nlev - 1) store_row(outv[l - 1] + (int64_t)r * pitchB, o);
+            if (!KEEP2 || (l >= nlev - 1 && outv[l - 1]))
+              store_row(outv[l - 1] + (int64_t)r * pitchB, o);
           if constexpr (MOM == kMomSelf) {
             const int q0 = 2 * (l - 1);
 #pragma unroll
@@ -815,6 +829,19 @@ __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts
                     b[v].y += car[v].y;
                   }
                 }
+                if constexpr (SEQ) {
+                  if (dot_carry) {
+#pragma unroll
+                    for (int v = 0; v < V; ++v) {
+                      const bool w = WHOLE ? true : own[v];
+                      const C q = w ? cd[v] : C{T(0), T(0)};
+                      sd[0] += q.x * b[v].x;
+                      sd[0] += q.y * b[v].y;
+                      sd[1] += q.x * b[v].y;
+                      sd[1] -= q.y * b[v].x;
+                    }
+                  }
+                }
                 if constexpr (WHOLE) {
                   if (lane_own) stv<V>((gT*)(carryb + so), b);
                 } else {
@@ -832,13 +859,15 @@ __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts
 #pragma unroll
           for (int l = 1; l <= KT; ++l) {
             if constexpr (STEADY) {
-              if (MOM != kMomNone && l < KT - 1) continue;
+              if (KEEP2 && l < KT - 1) continue;
             } else {
               if (l > lmax) break;
-              if (!owned_row(i - nlev - l) || (MOM != kMomNone && l < nlev - 1)) continue;
+              if (!owned_row(i - nlev - l) || (KEEP2 && l < nlev - 1)) continue;
             }
+            if constexpr (SEQ)
+              if (!outv[l - 1]) continue;            // a time step's last launch keeps none
             const C(&row)[V] = l < KT ? rr[l < KT ? l : 0][SHI] : olast;
-            if constexpr (MOM == kMomNone) stv_nt<V>((gT*)(outb[l - 1] + so), row);
+            if constexpr (!KEEP2) stv_nt<V>((gT*)(outb[l - 1] + so), row);
             else stv<V>((gT*)(outb[l - 1] + so), row);
           }
         }
@@ -877,12 +906,23 @@ __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts
       iter_range(std::false_type{}, 0, ia);
       iter_range(std::true_type{}, ia, ib);
       iter_range(std::false_type{}, ib, n_iter);
+      if (!lane_own) sd[0] = sd[1] = T(0);
     } else {
       iter_range(std::false_type{}, 0, n_iter);
     }
   };
   if (whole) run(std::true_type{});
   else run(std::false_type{});
+
+  if constexpr (SEQ) {
+    if (dot_carry) {                                 // one record per item
+      T x[2] = {sd[0], sd[1]};
+      const double v = static_cast<double>(wave_sums<2, 32>(x, lane));
+      if (lane == sum_lane<2>(0) || lane == sum_lane<2>(1))
+        st.partial[((int64_t)st.mom_slot * st.total_items + item) * 2 +
+                   (lane == sum_lane<2>(0) ? 0 : 1)] = v;
+    }
+  }
 
   if constexpr (MOM != kMomNone) {
     if (dots) {

@@ -13,6 +13,7 @@ hipError_t launch_cheb_f64s(int vec, int kt, bool honey, bool diag, const ChebIn
     case 201: CSP_CHEB_LAUNCH(double, 2, 1, cheb::kMomSelf, false); break;
     case 202: CSP_CHEB_LAUNCH(double, 2, 2, cheb::kMomSelf, false); break;
     case 204: CSP_CHEB_LAUNCH(double, 2, 4, cheb::kMomSelf, false); break;
+    case 208: CSP_CHEB_LAUNCH(double, 2, 8, cheb::kMomSelf, false); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

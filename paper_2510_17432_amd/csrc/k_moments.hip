@@ -12,7 +12,9 @@ namespace csp {
 
 // mu_n for n = 0..Nk of one instance.  dots row n holds the sums of the step
 // that produced order n: [0] <psi0|phi_n>, [1] <psi0|phi_{n-1}>,
-// [2] <phi_n|phi_n>, [3] <phi_n|phi_{n-1}>.
+// [2] <phi_n|phi_n>, [3] <phi_n|phi_{n-1}>.  halving 2: no product with psi0
+// was taken; mu_0 is C_0 = <psi0|psi0> (already in row 0 of corr) and mu_1 =
+// <phi_1|phi_0>, both real.
 __global__ void k_mom_assemble(const MomCorrInst* __restrict__ mc, int Nk, int halving) {
   const MomCorrInst& M = mc[blockIdx.y];
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
@@ -23,16 +25,21 @@ __global__ void k_mom_assemble(const MomCorrInst* __restrict__ mc, int Nk, int h
     const double* p = M.dots + ((int64_t)row * 4 * Rg + kind * Rg + r) * 2;
     return make_double2(p[0], p[1]);
   };
+  auto first = [&](int k) {               // mu_0, mu_1
+    if (halving < 2) return dot(1, 1 - k);
+    return k == 0 ? reinterpret_cast<const double2*>(M.corr)[M.col0 + r]
+                  : make_double2(dot(1, 3).x, 0.0);
+  };
   double2 mu;
   if (n == 0) {
-    mu = dot(1, 1);                       // <psi0|s_k>
+    mu = first(0);                        // <psi0|s_k>
   } else if (!halving || n == 1) {
-    mu = dot(n, 0);
+    mu = n == 1 ? first(1) : dot(n, 0);
   } else if ((n & 1) == 0) {              // mu_2k = 2 <phi_k|phi_k> - mu_0
-    const double2 a = dot(n / 2, 2), m0 = dot(1, 1);
+    const double2 a = dot(n / 2, 2), m0 = first(0);
     mu = make_double2(2.0 * a.x - m0.x, 2.0 * a.y - m0.y);
   } else {                                // mu_2k+1 = 2 <phi_k+1|phi_k> - mu_1
-    const double2 a = dot((n + 1) / 2, 3), m1 = dot(1, 0);
+    const double2 a = dot((n + 1) / 2, 3), m1 = first(1);
     mu = make_double2(2.0 * a.x - m1.x, 2.0 * a.y - m1.y);
   }
   reinterpret_cast<double2*>(M.mu)[(int64_t)n * Rg + r] = mu;

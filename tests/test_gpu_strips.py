@@ -78,3 +78,40 @@ def test_strip_forms_match_oracle(csp, ctx, spec):
                         d = np.max(np.abs(fin.cpu().numpy() - fin_ref)) * np.sqrt(c.N)
                         assert d < 5 * tol, what
     g.close()
+
+
+@pytest.mark.parametrize("tau", [np.pi, 0.01, 0.4, 7.0])
+@pytest.mark.parametrize("spec", LATS)
+def test_sequential_and_self_product_forms(csp, ctx, spec, tau):
+    """The sequential form (carried state and <psi0|psi> in the recursion's
+    epilogue; from 3 to 29 orders a step, so one launch, whole launches and
+    remainders) and the complex128 self products at 8 steps per launch.  Both
+    sum what the oracle sums in another order: 1e-10 as for complex128."""
+    print("[gpu] seq %s %dx%d tau %.2f" % (spec["kind"], spec["Lx"], spec["Ly"], tau), flush=True)
+    g = csp.Lattice(ctx, **spec)
+    rest = {k: v for k, v in spec.items() if k not in ("kind", "Lx", "Ly", "center")}
+    c = o.Lattice(spec["kind"], spec["Lx"], spec["Ly"], **rest)
+    R, Nt = 3, 19                       # two batches of step records, groups of 2 and 1 columns
+    psi = o.random_phase_states_fast(c.N, R, 29)
+    kw = dict(Hn=g.halfwidth, H0=spec.get("center", 0.0), tau=tau)
+    ref, _, fin_ref = o.propagate(c, psi, Nt, b=0, return_final=True, **kw)
+    p = torch.from_numpy(psi).to("cuda:0")
+    for norm in (False, True):
+        fin = torch.zeros_like(p)
+        corr, rep = csp.csp_propagate(ctx, g, p, csp.make_params(
+            Nt, mode="fp64_seq", tau_tilde=tau, check_norm=norm), final=fin)
+        torch.cuda.synchronize()
+        assert rep.contract_launches == 0 and rep.n_blocks == Nt
+        assert np.max(np.abs(corr.cpu().numpy() - ref)) < 1e-10
+        assert np.max(np.abs(fin.cpu().numpy() - fin_ref)) < 1e-10
+    for seg in (8, 40):
+        params = csp.make_params(Nt, mode="fp64_conc", tau_tilde=tau,
+                                 assembly=csp.CSP_ASSEMBLE_MOMENTS)
+        T = csp.Tuning()
+        T.spmm_vec, T.spmm_steps, T.spmm_seg_rows, T.contract_wg_per_cu = 2, 8, seg, 4
+        csp.csp_set_tuning(ctx, [g], [R], params, T)
+        corr, rep = csp.csp_propagate(ctx, g, p, params)
+        torch.cuda.synchronize()
+        assert rep.spmm_steps == 8
+        assert np.max(np.abs(corr.cpu().numpy() - ref)) < 1e-10
+    g.close()
