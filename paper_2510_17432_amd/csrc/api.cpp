@@ -631,11 +631,13 @@ ChebPlan plan_cheb(std::vector<ChebInst>& insts, bool fp64, bool mom, int n_cu, 
     p.seg_rows = round_rows(insts, p.ow, p.kt, n_cu);
   } else {
     // long segments amortise the 2 kt margin rows; keep >= 8 waves per CU,
-    // down to 4 rows (2 in the state forms, whose results do not depend on
-    // the segments as the FP32 moment sums do: 64 x 64 sites 14 -> 12 us)
+    // down to 4 rows, or 2 where that leaves at most one wave per SIMD (state
+    // forms, whose results do not depend on the segments as the FP32 moment
+    // sums do: 64 x 64 sites 14 -> 12 us a launch; with more waves the margin
+    // rows cost more than they save)
     p.seg_rows = 64;
-    while (p.seg_rows > (mom ? 4 : 2) && items_rows1 / p.seg_rows < (int64_t)n_cu * 8)
-      p.seg_rows /= 2;
+    while (p.seg_rows > 4 && items_rows1 / p.seg_rows < (int64_t)n_cu * 8) p.seg_rows /= 2;
+    if (!mom && p.seg_rows == 4 && items_rows1 / 2 <= (int64_t)n_cu * 4) p.seg_rows = 2;
   }
   // explicit matrices: a wave owns 128 rows of ell_ct columns; items are
   // the moment records, one per (column, 128-row chunk)
@@ -1214,7 +1216,7 @@ static csp_status propagate_impl(csp_context* c, const std::vector<InstIn>& ins,
     apply_layout(sp.back(), g);
   }
   const ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, tune ? tune->spmm_vec : 0,
-                                     tune ? tune->spmm_steps : (fp64 ? 4 : 8),
+                                     tune ? tune->spmm_steps : 8,
                                      tune ? tune->spmm_seg_rows : 0);
   const int kt = sp_plan.kt;
 
@@ -2230,7 +2232,7 @@ csp_status qe_state_based(csp_context* c, const csp_lattice* L, const void* dev_
   std::vector<ChebInst> sp;
   for (auto& g : groups)
     for (int d = 0; d < 2; ++d) sp.push_back(make_inst(L, g.Rg, fp64));
-  const ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, fp64 ? 4 : 8, 0);
+  const ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, 8, 0);
   const int kt = sp_plan.kt;
   int B64 = 1;
   while (B64 < rows) B64 *= 2;
@@ -2482,7 +2484,7 @@ extern "C" csp_status csp_quasi_eigenstates(csp_context* c, const csp_lattice* L
   }
   std::vector<ChebInst> sp;
   for (auto& g : groups) sp.push_back(make_inst(L, g.Rg, fp64));
-  const ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, fp64 ? 4 : 8, 0);
+  const ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, 8, 0);
   const int kt = sp_plan.kt;
 
   // Orders per contraction chunk: all of them when they fit, else a multiple
@@ -2679,8 +2681,7 @@ extern "C" csp_status csp_ec_correlation(csp_context* c, const csp_lattice* L, i
   const bool fp64 = P.mode == CSP_FP64_CONC;
   const int nE = n_E;
   if (nE < 1 || nE > 128) return fail(CSP_EINVAL, "need 1 <= n_E <= 128");
-  const int e_tile = fp64 ? ec64_tile(nE) : 32;
-  const int ldp = (int)ceil_div(nE, e_tile) * e_tile;
+  const int ldp = fp64 ? nE : (int)ceil_div(nE, 32) * 32;
   if (alpha != 0 && alpha != 1) return fail(CSP_EINVAL, "alpha must be 0 (x) or 1 (y)");
   if (R < 1) return fail(CSP_EINVAL, "R must be >= 1");
   if (P.Nt < 1 || P.Nt > (1 << 20)) return fail(CSP_EINVAL, "need 1 <= Nt <= 2^20");
@@ -2741,7 +2742,7 @@ extern "C" csp_status csp_ec_correlation(csp_context* c, const csp_lattice* L, i
   }
   std::vector<ChebInst> sp;
   for (auto& g : groups) sp.push_back(make_inst(L, g.Rg, fp64));
-  const ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, fp64 ? 4 : 8, 0);
+  const ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, 8, 0);
   const int kt = sp_plan.kt;
   const int64_t target_slices = std::max<int64_t>(1, (int64_t)c->n_cu * 4 / R);
   const int64_t slice_len = std::max<int64_t>(512, (ceil_div(N, target_slices) + 7) / 8 * 8);

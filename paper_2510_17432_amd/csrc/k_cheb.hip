@@ -21,8 +21,8 @@ CSP_CHEB_LAUNCHER(launch_cheb_f64q)
 #undef CSP_CHEB_LAUNCHER
 
 bool cheb_shape_supported(bool fp64, int vec, int kt, bool mom) {
-  // complex128: 8 steps per launch for the self products (one block) only
-  if (fp64) return vec == 2 && (kt == 1 || kt == 2 || kt == 4 || (kt == 8 && mom));
+  // (complex128 moments at 8 steps: the self products of one block only)
+  if (fp64) return vec == 2 && (kt == 1 || kt == 2 || kt == 4 || kt == 8);
   if (vec != 2 && vec != 4) return false;
   return kt == 1 || kt == 2 || kt == 4 || (kt == 8 && (!mom || vec == 2));
 }

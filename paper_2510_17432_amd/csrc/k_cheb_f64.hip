@@ -12,6 +12,7 @@ hipError_t launch_cheb_f64(int vec, int kt, bool honey, bool diag, const ChebIns
     case 201: CSP_CHEB_LAUNCH(double, 2, 1, cheb::kMomNone, false); break;
     case 202: CSP_CHEB_LAUNCH(double, 2, 2, cheb::kMomNone, false); break;
     case 204: CSP_CHEB_LAUNCH(double, 2, 4, cheb::kMomNone, false); break;
+    case 208: CSP_CHEB_LAUNCH(double, 2, 8, cheb::kMomNone, false); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -408,32 +408,48 @@ __global__ __launch_bounds__(256) void k_ec_moments_f32(const EcInst* __restrict
 }
 
 // ------------------------------------------------------------------ moments, FP64
-// Workgroup per (instance, column, slice) and tile of up to 16 energies, or
-// 24 when there are more than 16 (the energies split evenly over the tiles).
-// Per step of 32 orbitals the chunk's 128 orders and the tile's bras are
-// staged in LDS with coalesced loads (32 lanes read one 512-byte row);
-// thread t accumulates energies t % 8 + 8 q (q < 2, or 3 with 24-energy
-// tiles) against orders t / 8 + 32 p, p = 0..3, with FMAs: six LDS reads per
-// eight complex products with two energies (the kernel is bound by LDS
-// reads; one energy against eight orders took nine).
-constexpr int kEc64Row = 33;         // complex values per LDS row (padded)
+// The same two real products on v_mfma_f64_16x16x4: A = 16 orders x 4 floats
+// of the chunk (two orbitals), B = 4 floats x 16 moment columns.  The columns
+// are the tile's energies twice, X_E (real parts) then Z_E = i X_E (imaginary
+// parts), packed without a gap: 49 energies take 98 of 7 x 16 columns.
+// Workgroup per (instance, column, slice) and tile of up to 56 energies (the
+// energies split evenly over the tiles).  Per step of 16 orbitals the chunk's
+// 128 orders and the tile's bras are staged in LDS with coalesced loads (16
+// lanes read one 256-byte row, the next step's loads in flight); wave w owns
+// orders 32 w .. 32 w + 31 against all columns, so nine LDS reads of 8 bytes
+// a lane feed 14 MFMAs.  Z is X with the floats of a pair swapped and the
+// first negated, formed as the operand is read.
+//
+// What bounds it: the matrix units, at the rate of the FP64 vector units.
+// The form it replaces (FMAs, each thread two or three energies against four
+// orders: 1.5 bytes of LDS reads per operation against 0.3) was bound by
+// those reads.  131072 orbitals x 2 columns x 128 orders x 49 energies (13.2
+// GFLOP, 742 MB) on MI355X: 480 -> 294 us, 45 TFLOP/s.
+//
+// MFMA lane (i = lane % 16, k = lane / 16): A = order i, float k; B = float
+// k, column i; accumulator v = (order 4 v + k, column i).
+constexpr int kEc64Orb = 16;              // orbitals per staged step
+constexpr int kEc64Row = 2 * kEc64Orb + 2;   // doubles per LDS row: 32 lanes of a read hit 64 banks
+typedef double ed64x4 __attribute__((ext_vector_type(4)));
 
-template <int NE>
-__global__ __launch_bounds__(256) void k_ec_moments_f64(const EcInst* __restrict__ insts,
+template <int NT>                        // 16-column tiles: up to 8 NT energies
+__global__ __launch_bounds__(256, 2) void k_ec_moments_f64(const EcInst* __restrict__ insts,
                                                         EcArgs a) {
-  constexpr int NQ = NE > 16 ? 3 : NE > 8 ? 2 : 1;  // energies per thread
-  constexpr int TILE = ec64_tile(NE);                 // energies a tile can hold
-  __shared__ double2 sa[128 * kEc64Row];
-  __shared__ double2 sb[8 * NQ * kEc64Row];
+  constexpr int NE = 8 * NT;              // energies a tile can hold
+  constexpr int BR = (NE + 15) / 16;      // bra rows staged per thread
+  __shared__ __align__(16) double sa[128 * kEc64Row];
+  __shared__ __align__(16) double sb[16 * BR * kEc64Row];
   const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(tid >> 6));
   // logical workgroup (slice, energy tile), the tiles of a slice adjacent
-  // (one XCD, the same orders at the same time: L2 hits after the first);
-  // the energies split evenly over the tiles (49: 17 + 16 + 16)
-  const int n_et = (a.nE + TILE - 1) / TILE;
+  // (one XCD, the same orders at the same time: L2 hits after the first)
+  const int n_et = (a.nE + NE - 1) / NE;
   const int tw = (a.nE + n_et - 1) / n_et;
   const int64_t lwg = xcd_remap(blockIdx.x, gridDim.x);
   const int64_t wg = lwg / n_et;
   const int e0 = tw * static_cast<int>(lwg - wg * n_et);
+  const int ne = a.nE - e0 < tw ? a.nE - e0 : tw;   // energies of this tile (may be < 1)
   int ii = 0;
   while (ii + 1 < a.n_inst && wg >= insts[ii + 1].wg0) ++ii;
   const EcInst& I = insts[ii];
@@ -443,79 +459,101 @@ __global__ __launch_bounds__(256) void k_ec_moments_f64(const EcInst* __restrict
   const int64_t N = I.N;
   const int64_t s_beg = (int64_t)sl * I.slice_len;
   const int64_t s_end = s_beg + I.slice_len < N ? s_beg + I.slice_len : N;
-  const int col = tid & 31, rsub = tid >> 5;        // staging: orbital col of row 8 j + rsub
 
-  const double2* arow[16];
-  bool aok[16];
+  // staging: orbital so of rows 16 j + sr
+  const int so = tid & (kEc64Orb - 1), sr = tid / kEc64Orb;
+  const double2* arow[8];
+  bool aok[8];
 #pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    const int r = 8 * j + rsub;
+  for (int j = 0; j < 8; ++j) {
+    const int r = 16 * j + sr;
     aok[j] = r < a.n_cnt;
     arow[j] = static_cast<const double2*>(I.slots) +
               (int64_t)ring_slot((a.n_lo + (aok[j] ? r : 0)) % a.S, a.S, a.G) * I.slot_stride +
               (int64_t)c * N;
   }
-  const double2* brow[NQ];
-  bool bok[NQ];
+  const double2* brow[BR];
+  bool bok[BR];
 #pragma unroll
-  for (int j = 0; j < NQ; ++j) {
-    const int e = e0 + 8 * j + rsub;
-    bok[j] = e < a.nE && 8 * j + rsub < tw;
-    brow[j] = static_cast<const double2*>(I.bra) + ((int64_t)(bok[j] ? e : 0) * I.Rg + c) * N;
+  for (int j = 0; j < BR; ++j) {
+    const int e = 16 * j + sr;
+    bok[j] = e < ne;
+    brow[j] = static_cast<const double2*>(I.bra) + ((int64_t)(bok[j] ? e0 + e : 0) * I.Rg + c) * N;
   }
-  double2 ra[16], rb[NQ];
+  double2 ra[8], rb[BR];
   auto fetch = [&](int64_t s) {
-    const int64_t o = s + col;
+    const int64_t o = s + so;
     const bool in = o < s_end;
 #pragma unroll
-    for (int j = 0; j < 16; ++j) ra[j] = (aok[j] && in) ? arow[j][o] : make_double2(0.0, 0.0);
+    for (int j = 0; j < 8; ++j) ra[j] = (aok[j] && in) ? arow[j][o] : make_double2(0.0, 0.0);
 #pragma unroll
-    for (int j = 0; j < NQ; ++j) rb[j] = (bok[j] && in) ? brow[j][o] : make_double2(0.0, 0.0);
+    for (int j = 0; j < BR; ++j) rb[j] = (bok[j] && in) ? brow[j][o] : make_double2(0.0, 0.0);
   };
 
-  const int eq = tid & 7, og = tid >> 3;           // energies eq + 8 q, orders og + 32 p
-  double sr[NQ][4], si[NQ][4];
+  // operand addresses of this lane
+  const int li = lane & 15, lk = lane >> 4;
+  const double* pa = sa + (32 * wave + li) * kEc64Row + lk;
+  const double* pb[NT];
+  unsigned neg[NT];                       // sign bit to flip
 #pragma unroll
-  for (int q = 0; q < NQ; ++q)
+  for (int t = 0; t < NT; ++t) {
+    const int q = 16 * t + li;            // column: X of energy q, Z of energy q - ne
+    const bool z = q >= ne;
+    const int e = z ? (q - ne < ne ? q - ne : 0) : q;
+    pb[t] = sb + (e < 16 * BR ? e : 0) * kEc64Row + (z ? lk ^ 1 : lk);
+    neg[t] = z && (lk & 1) == 0 ? 0x80000000u : 0u;
+  }
+  ed64x4 acc[2][NT];
 #pragma unroll
-    for (int p = 0; p < 4; ++p) sr[q][p] = si[q][p] = 0.0;
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[m][t] = ed64x4{0.0, 0.0, 0.0, 0.0};
+  const bool active0 = 32 * wave < a.n_cnt;          // wave-uniform
   if (s_beg < s_end) fetch(s_beg);
-  for (int64_t s = s_beg; s < s_end; s += 32) {
+  for (int64_t s = s_beg; s < s_end; s += kEc64Orb) {
+    __syncthreads();                                 // previous step consumed
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      *reinterpret_cast<double2*>(&sa[(16 * j + sr) * kEc64Row + 2 * so]) = ra[j];
+#pragma unroll
+    for (int j = 0; j < BR; ++j)
+      *reinterpret_cast<double2*>(&sb[(16 * j + sr) * kEc64Row + 2 * so]) = rb[j];
     __syncthreads();
+    if (s + kEc64Orb < s_end) fetch(s + kEc64Orb);
+    if (active0) {
 #pragma unroll
-    for (int j = 0; j < 16; ++j) sa[(8 * j + rsub) * kEc64Row + col] = ra[j];
+      for (int k = 0; k < 2 * kEc64Orb; k += 4) {
+        const double a0 = pa[k], a1 = pa[16 * kEc64Row + k];
 #pragma unroll
-    for (int j = 0; j < NQ; ++j) sb[(8 * j + rsub) * kEc64Row + col] = rb[j];
-    __syncthreads();
-    if (s + 32 < s_end) fetch(s + 32);
-    if (eq < NE) {
-      for (int o = 0; o < 32; ++o) {
-        double2 x[NQ];
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) x[q] = sb[(eq + 8 * q) * kEc64Row + o];
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-          const double2 f = sa[(og + 32 * p) * kEc64Row + o];
-#pragma unroll
-          for (int q = 0; q < NQ; ++q) {
-            sr[q][p] = fma(x[q].x, f.x, fma(x[q].y, f.y, sr[q][p]));
-            si[q][p] = fma(x[q].x, f.y, fma(-x[q].y, f.x, si[q][p]));
-          }
+        for (int t = 0; t < NT; ++t) {
+          const unsigned long long u = __builtin_bit_cast(unsigned long long, pb[t][k]);
+          const double b = __builtin_bit_cast(
+              double, u ^ ((unsigned long long)neg[t] << 32));
+          acc[0][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b, acc[0][t], 0, 0, 0);
+          acc[1][t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b, acc[1][t], 0, 0, 0);
         }
       }
     }
   }
-  double2* out = static_cast<double2*>(I.partial) + ((int64_t)c * I.n_slices + sl) * a.K * a.ldp;
+  // partial sums [order][energy] (re, im): column q < ne the real part of
+  // energy q, ne <= q < 2 ne the imaginary part of energy q - ne
+  double* out = static_cast<double*>(I.partial) +
+                2 * ((int64_t)c * I.n_slices + sl) * (int64_t)a.K * a.ldp;
+  if (active0) {
 #pragma unroll
-  for (int q = 0; q < NQ; ++q) {
-    const int e = eq + 8 * q;
-    if (e < tw && e0 + e < a.nE) {
+    for (int m = 0; m < 2; ++m)
 #pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        const int r = og + 32 * p;
-        if (r < a.n_cnt) out[(int64_t)r * a.ldp + e0 + e] = make_double2(sr[q][p], si[q][p]);
+      for (int t = 0; t < NT; ++t) {
+        const int q = 16 * t + li;
+        const int e = q < ne ? q : q - ne, part = q < ne ? 0 : 1;
+        if (q < 2 * ne) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int r = 32 * wave + 16 * m + 4 * v + lk;
+            if (r < a.n_cnt) out[2 * ((int64_t)r * a.ldp + e0 + e) + part] = acc[m][t][v];
+          }
+        }
       }
-    }
   }
 }
 
@@ -560,23 +598,23 @@ __global__ __launch_bounds__(256) void k_ec_mu_finish(const EcInst* __restrict__
 
 hipError_t launch_ec_moments(bool fp64, const EcInst* d_inst, int n_inst, const EcArgs& a,
                              hipStream_t s) {
-  const int tile = fp64 ? ec64_tile(a.nE) : 32;
+  const int tile = fp64 ? kEc64Tile : 32;
   const int n_et = (int)ceil_div(a.nE, tile);
-  if (a.n_cnt < 1 || a.n_cnt > a.K || a.K > 128 || a.nE < 1 || a.ldp != n_et * tile)
+  if (a.n_cnt < 1 || a.n_cnt > a.K || a.K > 128 || a.nE < 1 || a.ldp < a.nE)
     return hipErrorInvalidValue;
   if (fp64) {
-    int ne = 1;
-    while (ne < std::min(a.nE, 16)) ne *= 2;
-    if (a.nE > 16) ne = 24;
-#define CSP_EC64(NE) \
-  hipLaunchKernelGGL(k_ec_moments_f64<NE>, dim3(a.total_wg * n_et), dim3(256), 0, s, d_inst, a)
-    switch (ne) {
+    // the energies of a tile, twice, in 16-column tiles
+    const int nt = (int)ceil_div(2 * ceil_div(a.nE, n_et), 16);
+#define CSP_EC64(NT) \
+  hipLaunchKernelGGL(k_ec_moments_f64<NT>, dim3(a.total_wg * n_et), dim3(256), 0, s, d_inst, a)
+    switch (nt) {
       case 1: CSP_EC64(1); break;
       case 2: CSP_EC64(2); break;
+      case 3: CSP_EC64(3); break;
       case 4: CSP_EC64(4); break;
-      case 8: CSP_EC64(8); break;
-      case 16: CSP_EC64(16); break;
-      default: CSP_EC64(24); break;
+      case 5: CSP_EC64(5); break;
+      case 6: CSP_EC64(6); break;
+      default: CSP_EC64(7); break;
     }
 #undef CSP_EC64
   } else {
