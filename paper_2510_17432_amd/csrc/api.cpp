@@ -107,6 +107,7 @@ struct csp_lattice {
   double box[2] = {0.0, 0.0};
   // windowed layout of an explicit matrix (see ell_windows.cpp); null when
   // the matrix's slices are not compact enough for it to pay
+  int ellw_nr = 0;                   // rows of a slice
   int32_t* ellw_rows = nullptr;
   uint16_t* ellw_loc = nullptr;
   int32_t* ellw_col = nullptr;
@@ -387,16 +388,28 @@ extern "C" csp_status csp_lattice_create_sparse(csp_context* c, int64_t N, int32
   {
     // The windowed layout pays when most slices name few distinct columns:
     // at least half of them with a window that fits a 4-column complex64
-    // workgroup's LDS and is read four or more times per step.
+    // workgroup in 64 KB of LDS and is read four or more times per step.
+    // Slices of 256 rows (windows 1.45 times those of 128 where the matrix is
+    // local, so fewer values staged per row and more rows on a CU) are taken
+    // for matrices that the 256 MB of last-level cache do not hold beside the
+    // vectors, from 160 MB in complex64 on: 1500^2 rows at D = 121, 5 columns
+    // 23.3 -> 21.9 ms for 16 time steps, 512^2 rows 10.8 -> 10.2 ms for 64.
+    // Below, the grid needs the 128-row workgroups (200^2 rows, 5 columns 4.0
+    // against 4.1 ms, 350^2, 4 columns 4.7 against 5.1 ms), and where windows
+    // pass 800 positions fewer workgroups fit a CU (512^2 rows at D = 233, 2
+    // columns: 10.9 ms with 128 rows, 13.2 ms with 256).
     EllWindows w;
-    build_ell_windows(N, D, col, val, &w);
-    const int64_t cap4 = kEllwLdsBytes / (4 * (int64_t)sizeof(float2));
-    int64_t good = 0;
-    for (int64_t k = 0; k < w.n_slices; ++k) {
-      const int64_t W = w.off[k + 1] - w.off[k];
-      if (W > 0 && W <= cap4 && 128 * (int64_t)D >= 4 * W) ++good;
-    }
-    if (2 * good >= w.n_slices) {
+    auto most = [&](int nr, int64_t cap) {
+      return [=](const std::vector<int32_t>& sizes) {
+        int64_t good = 0;
+        for (int64_t W : sizes)
+          if (W > 0 && W <= cap && nr * (int64_t)D >= 4 * W) ++good;
+        return 2 * good >= (int64_t)sizes.size();
+      };
+    };
+    if ((N * (int64_t)D * 6 >= 160 << 20 &&
+         build_ell_windows(N, D, col, val, 256, most(256, 800), &w)) ||
+        build_ell_windows(N, D, col, val, 128, most(128, 2048), &w)) {
       const size_t ne = w.loc.size();
       auto up = [&](void** dst, const void* src, size_t bytes) {
         if (e != hipSuccess) return;
@@ -415,9 +428,8 @@ extern "C" csp_status csp_lattice_create_sparse(csp_context* c, int64_t N, int32
         return cleanup(fail(CSP_ENOMEM, "windowed explicit matrix of %lld entries: %s",
                             (long long)ne, hipGetErrorString(e)));
       }
-      L->ellw_sizes.resize(w.n_slices);
-      for (int64_t k = 0; k < w.n_slices; ++k)
-        L->ellw_sizes[k] = static_cast<int32_t>(w.off[k + 1] - w.off[k]);
+      L->ellw_nr = w.nr;
+      L->ellw_sizes = w.sizes;
       L->ellw_sorted = L->ellw_sizes;
       std::sort(L->ellw_sorted.begin(), L->ellw_sorted.end());
     }
@@ -639,14 +651,15 @@ ChebPlan plan_cheb(std::vector<ChebInst>& insts, bool fp64, bool mom, int n_cu, 
     while (p.seg_rows > 4 && items_rows1 / p.seg_rows < (int64_t)n_cu * 8) p.seg_rows /= 2;
     if (!mom && p.seg_rows == 4 && items_rows1 / 2 <= (int64_t)n_cu * 4) p.seg_rows = 2;
   }
-  // explicit matrices: a wave owns 128 rows of ell_ct columns; items are
-  // the moment records, one per (column, 128-row chunk)
+  // explicit matrices: a wave owns 128 rows (a workgroup a windowed slice) of
+  // ell_ct columns; items are the moment records, one per (column, those rows)
   int64_t t0 = 0, w0 = 0;
   for (size_t k = 0; k < insts.size(); ++k) {
     ChebInst& I = insts[k];
     const bool sparse = I.kind == CSP_SPARSE;
     I.n_strips = sparse ? 1 : ceil_div(I.opr, p.ow);
-    I.n_segs = sparse ? ceil_div(I.N, 128) : ceil_div(I.Ly, p.seg_rows);
+    const int win = sparse && I.ellw_rows ? I.ellw_nr : 0;
+    I.n_segs = win ? I.ellw_ns : sparse ? ceil_div(I.N, 128) : ceil_div(I.Ly, p.seg_rows);
     I.item0 = t0;
     I.wave0 = w0;
     const int64_t n = (int64_t)I.Rg * I.n_strips * I.n_segs;
@@ -654,7 +667,6 @@ ChebPlan plan_cheb(std::vector<ChebInst>& insts, bool fp64, bool mom, int n_cu, 
     const int64_t nw = sparse ? I.n_segs * ceil_div(I.Rg, ct) : 0;
     const bool honey = I.kind == CSP_HONEYCOMB;
     const bool diag = I.eps != nullptr || I.beta0 != 0.0;
-    const bool win = sparse && I.ellw_rows != nullptr;
     if (p.runs.empty() || p.runs.back().honey != honey || p.runs.back().diag != diag ||
         p.runs.back().sparse != sparse || p.runs.back().ct != ct || p.runs.back().win != win)
       p.runs.push_back({(int)k, 0, t0, 0, honey, diag, sparse, ct, w0, 0, win, 0});
@@ -702,7 +714,9 @@ ChebInst make_inst(const csp_lattice* L, int Rg, bool fp64) {
     I.ell_ct = ell_columns_per_wave(fp64, Rg);
     if (L->ellw_rows) {
       const int64_t p97 = L->ellw_sorted[(L->ellw_sorted.size() * 97) / 100];
-      I.ell_ct = ellw_columns_per_group(fp64, Rg, p97);
+      I.ell_ct = ellw_columns_per_group(fp64, Rg, p97, L->ellw_nr, L->g.N * L->ell_D);
+      I.ellw_nr = L->ellw_nr;
+      I.ellw_ns = (int64_t)L->ellw_sizes.size();
       I.ellw_rows = L->ellw_rows;
       I.ellw_loc = L->ellw_loc;
       I.ellw_col = L->ellw_col;

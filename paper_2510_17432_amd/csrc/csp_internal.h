@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <functional>
 #include <vector>
 #include <stdint.h>
 
@@ -127,9 +128,11 @@ struct ChebInst {
   void* ell_shadow;
   int64_t sh_pairs;
   // explicit matrix, windowed layout (null: the slice layout above): slices
-  // of 128 rows compact in the matrix graph, [n_segs][128] rows, entries in
-  // quads [n_segs][ceil(D/4)][128][4] with window-local and global columns,
+  // of nr rows compact in the matrix graph, [n_segs][nr] rows, entries in
+  // quads [n_segs][ceil(D/4)][nr][4] with window-local and global columns,
   // per-slice windows (the distinct columns a slice names, ascending)
+  int32_t ellw_nr;             // rows of a slice (nr: 256 or 128)
+  int64_t ellw_ns;             // slices
   const int32_t* ellw_rows;    // row of each lane (-1: none)
   const uint16_t* ellw_loc;    // window-local column of each entry
   const int32_t* ellw_col;     // column of each entry (slices not staged)
@@ -171,7 +174,7 @@ struct ChebRun {
   bool honey, diag, sparse;   // diag: on-site energies or H0 != 0
   int ct;                      // explicit matrix: columns per wave (workgroup if windowed)
   int64_t wave0, n_waves;      // explicit matrix: waves (workgroups if windowed) of the run
-  bool win;                    // explicit matrix in the windowed layout
+  int win;                     // explicit matrix in the windowed layout: rows of a slice (else 0)
   int64_t win_cap;             // windowed: LDS complex values of the run's largest tile
 };
 // mom: moment epilogue; carry: the carried state (with moments, or alone: the
@@ -185,32 +188,38 @@ hipError_t launch_cheb_ell(bool fp64, bool mom, bool carry, int ct, const ChebIn
                            hipStream_t s);
 // columns per wave of the explicit-matrix kernel for a group of Rg columns
 int ell_columns_per_wave(bool fp64, int Rg);
-// Windowed layout: one workgroup of 128 threads per (slice, tile of ct
-// columns) stages the slice's window of phi_n in LDS (wg_lo .. wg_hi - 1
+// Windowed layout: one workgroup of nr threads per (slice of nr rows, tile of
+// ct columns) stages the slice's window of phi_n in LDS (wg_lo .. wg_hi - 1
 // over the run's instances, I.wave0 = first workgroup of an instance).
-hipError_t launch_cheb_ellw(bool fp64, bool mom, bool carry, int ct, int64_t lds_values,
+hipError_t launch_cheb_ellw(bool fp64, bool mom, bool carry, int ct, int nr, int64_t lds_values,
                             const ChebInst* d_inst, int n_inst, int64_t wg_lo, int64_t wg_hi,
                             const ChebStep& st, hipStream_t s);
 // columns per workgroup of the windowed kernel for a group of Rg columns
-// whose slices stage windows of up to `window` positions
-int ellw_columns_per_group(bool fp64, int Rg, int64_t window);
-// LDS bytes a windowed workgroup may stage
-constexpr int64_t kEllwLdsBytes = 64 * 1024;
+// whose slices of nr rows stage windows of up to `window` positions, the
+// matrix holding `entries` entries
+int ellw_columns_per_group(bool fp64, int Rg, int64_t window, int nr, int64_t entries);
+// LDS bytes a windowed workgroup may stage: two workgroups share a CU's 160 KB
+constexpr int64_t kEllwLdsBytes = 80 * 1024;
 
 // Host side of the windowed layout (built at lattice creation).
 struct EllWindows {
   int64_t n_slices = 0;
-  int64_t max_window = 0;
   int D4 = 0;                    // quads of entries per row
-  std::vector<int32_t> rows;     // [n_slices][128]
+  int nr = 0;                    // rows of a slice
+  std::vector<int32_t> rows;     // [n_slices][nr]
+  std::vector<int32_t> sizes;    // window size of every slice
   std::vector<int64_t> off;      // [n_slices + 1]
   std::vector<int32_t> idx;      // windows, ascending per slice
-  std::vector<uint16_t> loc;     // [n_slices][D4][128][4]
-  std::vector<int32_t> col;      // [n_slices][D4][128][4]
-  std::vector<double> v64;       // [n_slices][D4][128][4]
+  std::vector<uint16_t> loc;     // [n_slices][D4][nr][4]
+  std::vector<int32_t> col;      // [n_slices][D4][nr][4]
+  std::vector<double> v64;       // [n_slices][D4][nr][4]
   std::vector<float> v32;        // same, FP32
 };
-bool build_ell_windows(int64_t N, int D, const int32_t* col, const double* val, EllWindows* w);
+// Slices of nr rows with their windows; false, with only rows and sizes set,
+// when accept(sizes) refuses them.
+bool build_ell_windows(int64_t N, int D, const int32_t* col, const double* val, int nr,
+                       const std::function<bool(const std::vector<int32_t>&)>& accept,
+                       EllWindows* w);
 // max_s sum_k |val_sk| (k in order, FP64): one maximum per block into partial
 hipError_t launch_ell_gershgorin(int64_t N, int D, const double* d_val, double* d_partial,
                                  int n_partial, hipStream_t s);

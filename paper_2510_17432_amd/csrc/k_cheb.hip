@@ -52,7 +52,7 @@ hipError_t launch_cheb(bool fp64, int vec, int kt, bool mom, bool carry, const C
       e = r.sparse ? hipErrorInvalidValue
                    : launch_cheb_f64q(vec, kt, r.honey, r.diag, di, r.n_inst, lo, hi, st, s);
     else if (r.sparse && r.win)
-      e = launch_cheb_ellw(fp64, mom, carry, r.ct, r.win_cap, di, r.n_inst, r.wave0,
+      e = launch_cheb_ellw(fp64, mom, carry, r.ct, r.win, r.win_cap, di, r.n_inst, r.wave0,
                            r.wave0 + r.n_waves, st, s);
     else if (r.sparse)
       e = launch_cheb_ell(fp64, mom, carry, r.ct, di, r.n_inst, r.wave0, r.wave0 + r.n_waves, st,

@@ -2,11 +2,14 @@
 // Sec. II.B, for matrices of any density D_H):
 //   phi_{n+1} = 2 H~ phi_n - phi_{n-1},
 // one step per launch.  The layout (built at lattice creation,
-// ell_windows.cpp) groups the rows into slices of 128 that are compact in
-// the matrix graph and lists, per slice, its window: the distinct columns
-// its entries name.
+// ell_windows.cpp) groups the rows into slices of 256 or 128 that are
+// compact in the matrix graph and lists, per slice, its window: the distinct
+// columns its entries name.  512^2 rows at D = 121, 5 columns, complex64
+// moments: 93 -> 79 us a launch (190 MB of matrix, 2.4 TB/s) with 256-row
+// slices, no ragged ones and narrower tiles; what bounds it is the latency of
+// a slice (window, then 31 quads of entries) at 4 workgroups per CU.
 //
-// One workgroup of 128 threads owns a slice and a tile of CT columns of a
+// One workgroup, a thread per row, owns a slice and a tile of CT columns of a
 // column group.  It stages the slice's window of phi_n for its columns in
 // LDS (one plane of W complex values per column, coalesced where the
 // window's columns run consecutively), then thread t accumulates row t of
@@ -20,7 +23,7 @@
 // thread t reads and writes row rows[t] of phi_n, phi_{n-1}, phi_{n+1},
 // psi0 and the carried state (scattered within the slice's ball of rows).
 // Moment epilogue and carried state as the other recursion kernels: one
-// record of 8 FP64 sums per (column, slice), the two waves of the
+// record of 8 FP64 sums per (column, slice), the waves of the
 // workgroup added in a fixed order.
 #include <algorithm>
 #include <type_traits>
@@ -60,11 +63,11 @@ __device__ __forceinline__ void st(CSP_GLOBAL T* p, cplx<T> c, bool nt) {
 }
 
 template <typename T, int CT, bool MOM, bool CARRY>
-__global__ __launch_bounds__(128) void k_cheb_ellw(const ChebInst* __restrict__ insts, int n_inst,
+__global__ __launch_bounds__(256) void k_cheb_ellw(const ChebInst* __restrict__ insts, int n_inst,
                                                    int64_t wg_lo, int64_t wg_hi, ChebStep sp) {
   using C = cplx<T>;
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ double red[2][CT][8];                  // record sums of the two waves
+  const int nr = blockDim.x;                        // rows of a slice: 128 or 256
   const int t = threadIdx.x;
   const int lane = t & 63, wave = t >> 6;
   const int64_t L = wg_lo + xcd_remap(blockIdx.x, gridDim.x);
@@ -83,7 +86,7 @@ __global__ __launch_bounds__(128) void k_cheb_ellw(const ChebInst* __restrict__ 
   const int nc = tb + (tile < tr ? 1 : 0);          // columns of this tile
   const int64_t N = I.N;
   const int D = I.ell_D;
-  const int32_t row = I.ellw_rows[slice * 128 + t];
+  const int32_t row = I.ellw_rows[slice * nr + t];
   const bool valid = row >= 0;
   const int64_t woff = I.ellw_off[slice];
   const int64_t W = I.ellw_off[slice + 1] - woff;
@@ -115,10 +118,10 @@ __global__ __launch_bounds__(128) void k_cheb_ellw(const ChebInst* __restrict__ 
     constexpr int NC = decltype(nc_tag)::value;
     const CSP_GLOBAL int32_t* wi = (const CSP_GLOBAL int32_t*)(I.ellw_idx) + woff;
     int w = t;
-    for (; w + 3 * 128 < Wi; w += 4 * 128) {
+    for (; w + 3 * nr < Wi; w += 4 * nr) {
       int64_t j[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) j[u] = wi[w + u * 128];
+      for (int u = 0; u < 4; ++u) j[u] = wi[w + u * nr];
       C x[4][NC];
 #pragma unroll
       for (int u = 0; u < 4; ++u)
@@ -127,9 +130,9 @@ __global__ __launch_bounds__(128) void k_cheb_ellw(const ChebInst* __restrict__ 
 #pragma unroll
       for (int u = 0; u < 4; ++u)
 #pragma unroll
-        for (int c = 0; c < NC; ++c) win[c * Wi + w + u * 128] = x[u][c];
+        for (int c = 0; c < NC; ++c) win[c * Wi + w + u * nr] = x[u][c];
     }
-    for (; w < Wi; w += 128) {
+    for (; w < Wi; w += nr) {
       const int64_t j = wi[w];
       C x[NC];
 #pragma unroll
@@ -150,18 +153,18 @@ __global__ __launch_bounds__(128) void k_cheb_ellw(const ChebInst* __restrict__ 
 #pragma unroll
   for (int c = 0; c < CT; ++c) ar[c] = ai[c] = T(0);
   const int D4 = (D + 3) / 4;
-  const int64_t qofs = slice * D4 * 512 + 4 * t;    // quad 0 of this row
+  const int64_t qofs = (slice * D4 * nr + t) * 4;    // quad 0 of this row
   const CSP_GLOBAL T* vp = (const CSP_GLOBAL T*)(I.ellw_val) + qofs;
   auto ld_vals = [&](int q, T (&v)[4]) {
     if constexpr (sizeof(T) == 4) {
       const f32x4 a = __builtin_nontemporal_load(
-          reinterpret_cast<const CSP_GLOBAL f32x4*>(vp + (int64_t)q * 512));
+          reinterpret_cast<const CSP_GLOBAL f32x4*>(vp + (int64_t)q * (4 * nr)));
       v[0] = a.x;
       v[1] = a.y;
       v[2] = a.z;
       v[3] = a.w;
     } else {
-      const CSP_GLOBAL f64x2* p = reinterpret_cast<const CSP_GLOBAL f64x2*>(vp + (int64_t)q * 512);
+      const CSP_GLOBAL f64x2* p = reinterpret_cast<const CSP_GLOBAL f64x2*>(vp + (int64_t)q * (4 * nr));
       const f64x2 a = __builtin_nontemporal_load(p), b = __builtin_nontemporal_load(p + 1);
       v[0] = a.x;
       v[1] = a.y;
@@ -186,7 +189,7 @@ __global__ __launch_bounds__(128) void k_cheb_ellw(const ChebInst* __restrict__ 
 #pragma unroll
       for (int p = 0; p < NQ; ++p)
         if (p < D4) {
-          la[p] = __builtin_nontemporal_load(lp + (int64_t)p * 128);
+          la[p] = __builtin_nontemporal_load(lp + (int64_t)p * nr);
           ld_vals(p, va[p]);
         }
 #pragma unroll 1
@@ -196,7 +199,7 @@ __global__ __launch_bounds__(128) void k_cheb_ellw(const ChebInst* __restrict__ 
 #pragma unroll
         for (int p = 0; p < NQ; ++p)
           if (q0 + NQ + p < D4) {
-            lb[p] = __builtin_nontemporal_load(lp + (int64_t)(q0 + NQ + p) * 128);
+            lb[p] = __builtin_nontemporal_load(lp + (int64_t)(q0 + NQ + p) * nr);
             ld_vals(q0 + NQ + p, vb[p]);
           }
 #pragma unroll
@@ -225,12 +228,19 @@ __global__ __launch_bounds__(128) void k_cheb_ellw(const ChebInst* __restrict__ 
       }
     } else {
       // a window beyond the LDS budget: gather from the vectors, the NC x 4
-      // values of a quad issued together
+      // values of a quad issued together; with few columns the next quad's
+      // column numbers are loaded before them (64 steps: 400^2 rows, 1 column
+      // 12.4 -> 10.2 ms; 512^2, 5 columns 10.2 -> 13.5 ms, so not there)
+      constexpr bool AHEAD = NC <= 3;
       const CSP_GLOBAL i32x4* gp = reinterpret_cast<const CSP_GLOBAL i32x4*>(
           (const CSP_GLOBAL int32_t*)(I.ellw_col) + qofs);
+      i32x4 jn = {0, 0, 0, 0};
+      if constexpr (AHEAD) jn = __builtin_nontemporal_load(gp);
 #pragma unroll 1
       for (int q = 0; q < D4; ++q) {
-        const i32x4 j4 = __builtin_nontemporal_load(gp + (int64_t)q * 128);
+        i32x4 j4 = jn;
+        if constexpr (!AHEAD) j4 = __builtin_nontemporal_load(gp + (int64_t)q * nr);
+        else if (q + 1 < D4) jn = __builtin_nontemporal_load(gp + (int64_t)(q + 1) * nr);
         T v[4];
         ld_vals(q, v);
         const int64_t jj[4] = {j4.x, j4.y, j4.z, j4.w};
@@ -261,7 +271,7 @@ __global__ __launch_bounds__(128) void k_cheb_ellw(const ChebInst* __restrict__ 
       T v[4];
       ld_vals(q, v);
       for (int e = 0; e < 4; ++e) {
-        const int64_t j = gp[(int64_t)q * 512 + e];
+        const int64_t j = gp[(int64_t)q * (4 * nr) + e];
         for (int c = 0; c < nc; ++c) {
           const C x = ld<T>(cur + 2 * ((int64_t)c * N + j));
           ar[c] = fma(v[e], x.x, ar[c]);
@@ -276,6 +286,9 @@ __global__ __launch_bounds__(128) void k_cheb_ellw(const ChebInst* __restrict__ 
   const T alpha = scale * static_cast<T>(I.alpha);
   const T beta0 = scale * static_cast<T>(I.beta0);
   const bool dots = MOM && (sp.dot_psi0 || sp.dot_self);
+  // record sums of the waves, in the window's place
+  double* red = reinterpret_cast<double*>(smem);
+  if (dots) __syncthreads();
 #pragma unroll
   for (int c = 0; c < CT; ++c) {
     double rec[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -329,7 +342,7 @@ __global__ __launch_bounds__(128) void k_cheb_ellw(const ChebInst* __restrict__ 
           double x = rec[q];
 #pragma unroll
           for (int m = 32; m >= 1; m >>= 1) x += __shfl_xor(x, m);
-          if (lane == q) red[wave][c][q] = x;
+          if (lane == q) red[(wave * CT + c) * 8 + q] = x;
         }
       }
     }
@@ -342,7 +355,8 @@ __global__ __launch_bounds__(128) void k_cheb_ellw(const ChebInst* __restrict__ 
         if (c < nc) {
           const int64_t item = I.item0 + (int64_t)(c0 + c) * I.n_segs + slice;
           sp.partial[((int64_t)sp.mom_slot * sp.total_items + item) * 8 + q] =
-              red[0][c][q] + red[1][c][q];
+              nr == 256 ? ((red[t] + red[8 * CT + t]) + red[16 * CT + t]) + red[24 * CT + t]
+                        : red[t] + red[8 * CT + t];
         }
       }
     }
@@ -355,27 +369,38 @@ __global__ __launch_bounds__(128) void k_cheb_ellw(const ChebInst* __restrict__ 
 // as possible, split evenly (10 columns: two tiles of 5; 25: 7 + 6 + 6 + 6),
 // so the matrix is read once per step per tile and every tile holds CT or
 // CT - 1 columns.  A tile holds at most 8 columns, and at most as many as
-// fit the LDS budget with a window of `window` positions.
-int ellw_columns_per_group(bool fp64, int Rg, int64_t window) {
+// fit the LDS budget with a window of `window` positions.  A matrix that
+// stays in the 256 MB of last-level cache is read again by further tiles at
+// little cost, and narrow tiles put more workgroups on the chip (fewer
+// registers, less LDS): at most 3 columns up to 128 MB, 4 up to 256 MB (5
+// with slices of 256 rows).  Measured, 64 time steps of the moment form:
+// 200^2 rows at D = 121, 5 columns as one tile 5.0 ms, as 3 + 2 4.0 ms;
+// 480^2 at D = 61, 9 columns as 5 + 4 10.0, as 3 + 3 + 3 8.9 ms; complex128,
+// 200^2 at D = 28, 8 columns 4.3 and 2.6 ms; but from HBM, 1500^2 at D = 121,
+// 5 columns (16 steps) 23.3 and 29.5 ms.
+int ellw_columns_per_group(bool fp64, int Rg, int64_t window, int nr, int64_t entries) {
   const int64_t fit = kEllwLdsBytes / (std::max<int64_t>(window, 1) * (fp64 ? 16 : 8));
-  const int cap = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(8, fit)));
+  const int64_t mb = (entries * (fp64 ? 10 : 6)) >> 20;
+  const int64_t most = mb > 256 ? 8 : nr == 256 ? 5 : mb > 128 ? 4 : 3;
+  const int cap = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(most, fit)));
   if (Rg < 1) return 1;
   const int tiles = (Rg + cap - 1) / cap;
   return (Rg + tiles - 1) / tiles;
 }
 
-hipError_t launch_cheb_ellw(bool fp64, bool mom, bool carry, int ct, int64_t lds_cap,
+hipError_t launch_cheb_ellw(bool fp64, bool mom, bool carry, int ct, int nr, int64_t lds_cap,
                             const ChebInst* d_inst, int n_inst, int64_t wg_lo, int64_t wg_hi,
                             const ChebStep& st, hipStream_t s) {
   const int64_t n = wg_hi - wg_lo;
   if (n <= 0) return hipSuccess;
   if (st.nlev != 1 || (carry && !mom)) return hipErrorInvalidValue;
-  if (ct < 1 || ct > 8) return hipErrorInvalidValue;
+  if (ct < 1 || ct > 8 || (nr != 128 && nr != 256)) return hipErrorInvalidValue;
   // LDS: the largest staged window of the run's instances times its
   // columns (lds_cap complex values)
-  const size_t lds = (size_t)(lds_cap > 0 ? lds_cap : 1) * (fp64 ? 16 : 8);
+  const size_t lds = std::max<size_t>((size_t)(lds_cap > 0 ? lds_cap : 1) * (fp64 ? 16 : 8),
+                                      mom ? (size_t)(nr / 64) * ct * 64 : 0);
   if (lds > (size_t)kEllwLdsBytes) return hipErrorInvalidValue;
-  const dim3 grid(static_cast<unsigned>(n)), block(128);
+  const dim3 grid(static_cast<unsigned>(n)), block(nr);
 #define CSP_ELLW(T, CT, M, CY) \
   hipLaunchKernelGGL((ellw::k_cheb_ellw<T, CT, M, CY>), grid, block, lds, s, d_inst, n_inst, wg_lo, wg_hi, st)
 #define CSP_ELLW_CT(T, M, CY)      \
