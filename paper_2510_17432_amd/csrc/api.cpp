@@ -1430,6 +1430,7 @@ static csp_status propagate_impl(csp_context* c, const std::vector<InstIn>& ins,
   ca.G = RG;
   ca.jtiles = jtiles;
   ca.total_wg = total_wg;
+  ca.aligned = contract_aligned(ct.data(), ct.size());
   const ChebStep st0 = step_args(sp_plan);
 
   // One time block: recursion launches of up to kt steps each, with the
@@ -3207,6 +3208,7 @@ extern "C" csp_status csp_autotune(csp_context* c, int32_t n_inst, const csp_lat
   T.t_order_us[0] = T.t_order_us[1] = -1.0;
   if (!mom && K_t >= 16) {
     const int jt_max = fp64 ? 1 : kMaxJTiles;
+    int aligned = 0;
     auto setup = [&](int wpc, int* total) -> csp_status {
       std::vector<ContractInst> ct;
       int64_t Msum = 0;
@@ -3233,6 +3235,7 @@ extern "C" csp_status csp_autotune(csp_context* c, int32_t n_inst, const csp_lat
       }
       HIPCALL(hipMemcpyAsync(d_con, ct.data(), sizeof(ContractInst) * ct.size(),
                              hipMemcpyHostToDevice, s));
+      aligned = contract_aligned(ct.data(), ct.size());
       *total = wg0;
       return CSP_OK;
     };
@@ -3254,6 +3257,7 @@ extern "C" csp_status csp_autotune(csp_context* c, int32_t n_inst, const csp_lat
       ca.jtiles = jt;
       ca.bcols = fp64 ? kMaxFp64B : 32 * jt;
       ca.total_wg = total;
+      ca.aligned = aligned;
       if (fp64) {
         ca.coef = d_bop1;
         ca.ccarry = d_cc1;

@@ -351,11 +351,19 @@ struct ContractArgs {
   int32_t jtiles;           // 32-wide time tiles (FP32 MFMA path)
   int32_t bcols;            // time points of the block (b_k)
   int32_t total_wg;
+  int32_t aligned;          // FP32 path: contract_aligned() of the instances
   const void* bop;          // FP32 path: B operands in MFMA lane layout
   const void* coef;         // FP64 path: complex c[n][j], [n_cnt][bcols]
   const void* ccarry;       // carry coefficients: float a_n (FP32 path) or complex double (FP64)
 };
 
+// Whether the columns of the instances start at 16-byte boundaries (their
+// arrays do): rows padded to 16 values do, packed columns of odd N do not.
+inline bool contract_aligned(const ContractInst* inst, size_t n) {
+  for (size_t i = 0; i < n; ++i)
+    if (inst[i].N < 2 || inst[i].N % 2 || inst[i].slot_stride % 2) return false;
+  return true;
+}
 hipError_t launch_contract_f32(const ContractInst* d_inst, const ContractArgs& a, hipStream_t s);
 hipError_t launch_contract_f64(const ContractInst* d_inst, const ContractArgs& a, hipStream_t s);
 
