@@ -683,6 +683,28 @@ ChebPlan plan_cheb(std::vector<ChebInst>& insts, bool fp64, bool mom, int n_cu, 
   return p;
 }
 
+// Whether every lattice is a ribbon of at most `rows` rows, open in y, and all
+// of them give more than one wave per SIMD.  (Chains run without a row loop.)
+bool wide_ribbons(const std::vector<ChebInst>& insts, int64_t rows, int n_cu) {
+  int64_t waves = 0;
+  for (auto& I : insts) {
+    const bool chain = I.Ly == 1 && I.kind != CSP_HONEYCOMB;
+    if (I.kind == CSP_SPARSE || I.py || I.Ly > rows || chain) return false;
+    waves += I.Rg * ceil_div(I.opr, 64 * 2 - 2 * cheb_margin(2, 8));
+  }
+  return waves > 4 * (int64_t)n_cu;
+}
+
+// Steps per launch of the recursion (states, self products): 8, or 4 in
+// complex128 for wide ribbons of up to six rows.  Their rows run in the general
+// form, which computes 2 kt margin rows beside them: honeycomb 300000 x 4 cells
+// x 2 columns, one block of 32 steps by self products 2.42 ms with 8 steps per
+// launch, 1.63 with 4, two blocks of states 12.4 and 12.2 ms; with eight rows
+// the states take 22.1 and 24.0 ms, and 3000 x 4 cells 1.24 and 1.36 ms.
+int recursion_steps(const std::vector<ChebInst>& insts, bool fp64, int n_cu) {
+  return fp64 && wide_ribbons(insts, 6, n_cu) ? 4 : 8;
+}
+
 // Bytes of the per-orbital operands that every recursion launch reads once
 // per column group: on-site energies, or the explicit matrix (indices and
 // values).
@@ -1054,6 +1076,24 @@ static csp_status propagate_moments_impl(csp_context* c, const std::vector<InstI
 static csp_status propagate_seq_impl(csp_context* c, const std::vector<InstIn>& ins,
                                      const csp_params& P, double t_start, csp_report* rep);
 
+// Whether a sequential call accumulates the carried state in the recursion.
+// Explicit matrices (one step per launch: the carried state would be read and
+// written at every step, two vectors against one), calls that replay a graph
+// and wide ribbons of one or two rows (14 margin rows beside them: honeycomb
+// 300000 x 1 cells, 2 columns, W > 0, 32 steps 16.4 ms, 11.1 by the ring; with
+// four rows 25.9 and 32.0) keep the ring and the contraction.
+static bool seq_form(const csp_context* c, const std::vector<InstIn>& ins, const csp_params& P,
+                     bool batch_call) {
+  if (P.mode != CSP_FP64_SEQ || P.assembly != CSP_ASSEMBLE_STATES) return false;
+  if (P.graph > 0 || (P.graph == 0 && ins.size() > 1 && batch_call)) return false;
+  std::vector<ChebInst> insts;
+  for (auto& in : ins) {
+    if (in.lat->g.kind == CSP_SPARSE) return false;
+    insts.push_back(make_inst(in.lat, in.R, true));
+  }
+  return !wide_ribbons(insts, 2, c->n_cu);
+}
+
 // Column windows.  Every column is propagated independently, so when even
 // the smallest workspace (a 16-order chunk plus psi0 and carry for the
 // state assembly, 3 vectors plus psi0 and two carries for the moment
@@ -1151,15 +1191,7 @@ static csp_status propagate_impl(csp_context* c, const std::vector<InstIn>& ins,
     }
   }
   if (P.assembly == CSP_ASSEMBLE_MOMENTS) return propagate_moments_impl(c, ins, P, t_start, rep);
-  // The sequential form of stencil lattices accumulates the carried state in
-  // the recursion.  Explicit matrices (one step per launch: the carried state
-  // would be read and written at every step, two vectors against one) and
-  // calls that replay a graph keep the ring and the contraction.
-  if (P.mode == CSP_FP64_SEQ && !(P.graph > 0 || (P.graph == 0 && ins.size() > 1 && batch_call))) {
-    bool stencil = true;
-    for (auto& in : ins) stencil = stencil && in.lat->g.kind != CSP_SPARSE;
-    if (stencil) return propagate_seq_impl(c, ins, P, t_start, rep);
-  }
+  if (seq_form(c, ins, P, batch_call)) return propagate_seq_impl(c, ins, P, t_start, rep);
   const bool fp64 = P.mode != CSP_FP32_CONC;
   const size_t csz = fp64 ? sizeof(double2) : sizeof(float2);
   for (size_t i = 0; i < ins.size(); ++i) {
@@ -1230,7 +1262,7 @@ static csp_status propagate_impl(csp_context* c, const std::vector<InstIn>& ins,
     apply_layout(sp.back(), g);
   }
   const ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, tune ? tune->spmm_vec : 0,
-                                     tune ? tune->spmm_steps : 8,
+                                     tune ? tune->spmm_steps : recursion_steps(sp, fp64, c->n_cu),
                                      tune ? tune->spmm_seg_rows : 0);
   const int kt = sp_plan.kt;
 
@@ -1700,9 +1732,9 @@ static csp_status propagate_moments_impl(csp_context* c, const std::vector<InstI
   }
   const csp_tuning* tune = find_tuning(c, ins, fp64, CSP_ASSEMBLE_MOMENTS);
   int vec_want = tune ? tune->spmm_vec : 0;
-  // default: 8 steps per launch for the complex64 self-product kernel
-  // (halving), 4 where psi0 or the carried state take registers
-  int kt_want = tune ? tune->spmm_steps : (halving ? 8 : 4);
+  // default: 8 steps per launch for the self-product kernels (halving), 4
+  // where psi0 or the carried state take registers
+  int kt_want = tune ? tune->spmm_steps : !halving ? 4 : recursion_steps(sp, fp64, c->n_cu);
   if (carry && !cheb_carry_supported(fp64, 2, kt_want)) kt_want = 4;
   if (carry) vec_want = 2;   // the carried-state kernels hold 2 values per lane
   const ChebPlan sp_plan = plan_cheb(sp, fp64, true, c->n_cu, vec_want, kt_want,
@@ -2247,7 +2279,7 @@ csp_status qe_state_based(csp_context* c, const csp_lattice* L, const void* dev_
   std::vector<ChebInst> sp;
   for (auto& g : groups)
     for (int d = 0; d < 2; ++d) sp.push_back(make_inst(L, g.Rg, fp64));
-  const ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, 8, 0);
+  const ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, recursion_steps(sp, fp64, c->n_cu), 0);
   const int kt = sp_plan.kt;
   int B64 = 1;
   while (B64 < rows) B64 *= 2;
@@ -2499,7 +2531,7 @@ extern "C" csp_status csp_quasi_eigenstates(csp_context* c, const csp_lattice* L
   }
   std::vector<ChebInst> sp;
   for (auto& g : groups) sp.push_back(make_inst(L, g.Rg, fp64));
-  const ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, 8, 0);
+  const ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, recursion_steps(sp, fp64, c->n_cu), 0);
   const int kt = sp_plan.kt;
 
   // Orders per contraction chunk: all of them when they fit, else a multiple
@@ -2757,7 +2789,7 @@ extern "C" csp_status csp_ec_correlation(csp_context* c, const csp_lattice* L, i
   }
   std::vector<ChebInst> sp;
   for (auto& g : groups) sp.push_back(make_inst(L, g.Rg, fp64));
-  const ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, 8, 0);
+  const ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, recursion_steps(sp, fp64, c->n_cu), 0);
   const int kt = sp_plan.kt;
   const int64_t target_slices = std::max<int64_t>(1, (int64_t)c->n_cu * 4 / R);
   const int64_t slice_len = std::max<int64_t>(512, (ceil_div(N, target_slices) + 7) / 8 * 8);
