@@ -714,7 +714,8 @@ double static_bytes(const csp_lattice* L, bool fp64) {
   return L->has_onsite ? (double)L->g.N * w : 0.0;
 }
 
-ChebInst make_inst(const csp_lattice* L, int Rg, bool fp64) {
+// ring: the form keeps its orders in a ring (not the moment forms)
+ChebInst make_inst(const csp_lattice* L, int Rg, bool fp64, bool ring) {
   ChebInst I{};
   I.kind = L->g.kind;
   I.px = L->g.px;
@@ -736,7 +737,8 @@ ChebInst make_inst(const csp_lattice* L, int Rg, bool fp64) {
     I.ell_ct = ell_columns_per_wave(fp64, Rg);
     if (L->ellw_rows) {
       const int64_t p97 = L->ellw_sorted[(L->ellw_sorted.size() * 97) / 100];
-      I.ell_ct = ellw_columns_per_group(fp64, Rg, p97, L->ellw_nr, L->g.N * L->ell_D);
+      I.ell_ct = ellw_columns_per_group(fp64, ring, Rg, p97, L->ellw_nr,
+                                        (int64_t)L->ellw_sizes.size(), L->g.N * L->ell_D);
       I.ellw_nr = L->ellw_nr;
       I.ellw_ns = (int64_t)L->ellw_sizes.size();
       I.ellw_rows = L->ellw_rows;
@@ -837,7 +839,7 @@ extern "C" csp_status csp_chebyshev_step(csp_context* c, const csp_lattice* L, i
   const int64_t N = L->g.N;
   // the step runs on column-major copies: slot 0 = x, slot 1 = y in, slot 2 = y out
   const int64_t stride = (N * R + 63) / 64 * 64;
-  std::vector<ChebInst> insts(1, make_inst(L, R, fp64));
+  std::vector<ChebInst> insts(1, make_inst(L, R, fp64, true));
   ChebPlan p = plan_cheb(insts, fp64, false, c->n_cu);
   CHECK(ws_reserve(c, 3 * align256(stride * csz) + align256(sizeof(ChebInst))));
   Carver cv(c->ws);
@@ -1089,7 +1091,7 @@ static bool seq_form(const csp_context* c, const std::vector<InstIn>& ins, const
   std::vector<ChebInst> insts;
   for (auto& in : ins) {
     if (in.lat->g.kind == CSP_SPARSE) return false;
-    insts.push_back(make_inst(in.lat, in.R, true));
+    insts.push_back(make_inst(in.lat, in.R, true, true));
   }
   return !wide_ribbons(insts, 2, c->n_cu);
 }
@@ -1258,7 +1260,7 @@ static csp_status propagate_impl(csp_context* c, const std::vector<InstIn>& ins,
   // recursion launch shape (steps per launch kt)
   std::vector<ChebInst> sp;
   for (auto& g : groups) {
-    sp.push_back(make_inst(ins[g.inst].lat, g.Rg, fp64));
+    sp.push_back(make_inst(ins[g.inst].lat, g.Rg, fp64, true));
     apply_layout(sp.back(), g);
   }
   const ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, tune ? tune->spmm_vec : 0,
@@ -1727,7 +1729,7 @@ static csp_status propagate_moments_impl(csp_context* c, const std::vector<InstI
   }
   std::vector<ChebInst> sp;
   for (auto& g : groups) {
-    sp.push_back(make_inst(ins[g.inst].lat, g.Rg, fp64));
+    sp.push_back(make_inst(ins[g.inst].lat, g.Rg, fp64, false));
     apply_layout(sp.back(), g);
   }
   const csp_tuning* tune = find_tuning(c, ins, fp64, CSP_ASSEMBLE_MOMENTS);
@@ -2031,7 +2033,7 @@ static csp_status propagate_seq_impl(csp_context* c, const std::vector<InstIn>& 
   }
   std::vector<ChebInst> sp;
   for (auto& g : groups) {
-    sp.push_back(make_inst(ins[g.inst].lat, g.Rg, true));
+    sp.push_back(make_inst(ins[g.inst].lat, g.Rg, true, true));
     apply_layout(sp.back(), g);
   }
   const csp_tuning* tune = find_tuning(c, ins, true, CSP_ASSEMBLE_STATES);
@@ -2278,7 +2280,7 @@ csp_status qe_state_based(csp_context* c, const csp_lattice* L, const void* dev_
   }
   std::vector<ChebInst> sp;
   for (auto& g : groups)
-    for (int d = 0; d < 2; ++d) sp.push_back(make_inst(L, g.Rg, fp64));
+    for (int d = 0; d < 2; ++d) sp.push_back(make_inst(L, g.Rg, fp64, true));
   const ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, recursion_steps(sp, fp64, c->n_cu), 0);
   const int kt = sp_plan.kt;
   int B64 = 1;
@@ -2530,7 +2532,7 @@ extern "C" csp_status csp_quasi_eigenstates(csp_context* c, const csp_lattice* L
     }
   }
   std::vector<ChebInst> sp;
-  for (auto& g : groups) sp.push_back(make_inst(L, g.Rg, fp64));
+  for (auto& g : groups) sp.push_back(make_inst(L, g.Rg, fp64, true));
   const ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, recursion_steps(sp, fp64, c->n_cu), 0);
   const int kt = sp_plan.kt;
 
@@ -2788,7 +2790,7 @@ extern "C" csp_status csp_ec_correlation(csp_context* c, const csp_lattice* L, i
     }
   }
   std::vector<ChebInst> sp;
-  for (auto& g : groups) sp.push_back(make_inst(L, g.Rg, fp64));
+  for (auto& g : groups) sp.push_back(make_inst(L, g.Rg, fp64, true));
   const ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, recursion_steps(sp, fp64, c->n_cu), 0);
   const int kt = sp_plan.kt;
   const int64_t target_slices = std::max<int64_t>(1, (int64_t)c->n_cu * 4 / R);
@@ -3096,7 +3098,7 @@ extern "C" csp_status csp_autotune(csp_context* c, int32_t n_inst, const csp_lat
   }
   std::vector<ChebInst> sp;
   for (auto& g : groups) {
-    sp.push_back(make_inst(ins[g.inst].lat, g.Rg, fp64));
+    sp.push_back(make_inst(ins[g.inst].lat, g.Rg, fp64, !mom));
     apply_layout(sp.back(), g);
   }
 

@@ -195,9 +195,10 @@ hipError_t launch_cheb_ellw(bool fp64, bool mom, bool carry, int ct, int nr, int
                             const ChebInst* d_inst, int n_inst, int64_t wg_lo, int64_t wg_hi,
                             const ChebStep& st, hipStream_t s);
 // columns per workgroup of the windowed kernel for a group of Rg columns
-// whose slices of nr rows stage windows of up to `window` positions, the
-// matrix holding `entries` entries
-int ellw_columns_per_group(bool fp64, int Rg, int64_t window, int nr, int64_t entries);
+// whose `slices` slices of nr rows stage windows of up to `window` positions,
+// the matrix holding `entries` entries (ring: a form that keeps its orders)
+int ellw_columns_per_group(bool fp64, bool ring, int Rg, int64_t window, int nr, int64_t slices,
+                           int64_t entries);
 // LDS bytes a windowed workgroup may stage: two workgroups share a CU's 160 KB
 constexpr int64_t kEllwLdsBytes = 80 * 1024;
 

@@ -26,6 +26,7 @@
 // record of 8 FP64 sums per (column, slice), the waves of the
 // workgroup added in a fixed order.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "csp_internal.h"
@@ -365,27 +366,100 @@ __global__ __launch_bounds__(256) void k_cheb_ellw(const ChebInst* __restrict__ 
 
 }  // namespace ellw
 
-// Columns per workgroup (tile width CT): the group's columns in as few tiles
-// as possible, split evenly (10 columns: two tiles of 5; 25: 7 + 6 + 6 + 6),
-// so the matrix is read once per step per tile and every tile holds CT or
-// CT - 1 columns.  A tile holds at most 8 columns, and at most as many as
-// fit the LDS budget with a window of `window` positions.  A matrix that
-// stays in the 256 MB of last-level cache is read again by further tiles at
-// little cost, and narrow tiles put more workgroups on the chip (fewer
-// registers, less LDS): at most 3 columns up to 128 MB, 4 up to 256 MB (5
-// with slices of 256 rows).  Measured, 64 time steps of the moment form:
-// 200^2 rows at D = 121, 5 columns as one tile 5.0 ms, as 3 + 2 4.0 ms;
-// 480^2 at D = 61, 9 columns as 5 + 4 10.0, as 3 + 3 + 3 8.9 ms; complex128,
-// 200^2 at D = 28, 8 columns 4.3 and 2.6 ms; but from HBM, 1500^2 at D = 121,
-// 5 columns (16 steps) 23.3 and 29.5 ms.
-int ellw_columns_per_group(bool fp64, int Rg, int64_t window, int nr, int64_t entries) {
-  const int64_t fit = kEllwLdsBytes / (std::max<int64_t>(window, 1) * (fp64 ? 16 : 8));
+// Columns per workgroup (tile width CT): the group's columns in tiles split
+// evenly (25 in four: 7 + 6 + 6 + 6), so every tile holds CT or CT - 1
+// columns, at most 8 and at most as many as fit the LDS budget with a window
+// of `window` positions.  Every tile reads the matrix once per step (at
+// little cost while it stays in the 256 MB of last-level cache); narrow tiles
+// take fewer registers and less LDS.  The rule, with `waves` = waves per CU of
+// one tile of all slices; figures are calls of 24 time steps of the moment
+// form at the stated rows, D and columns (MI355X, ms):
+//
+// complex64, slices of 128 rows: a launch lasts as many rounds as its waves
+// need, so the fewest tiles whose workgroups are all resident at once
+// (registers, LDS) and that give a CU seven waves, except up to three columns
+// in one tile (160000 rows, D = 61, 7 columns: 2.86 in one tile, 3.14 as
+// 3 + 2 + 2 in two rounds; 90000, D = 121, 8 columns: 3.05 as 4 + 4, 3.57 as
+// 3 + 3 + 2); tiles of 4 and 6 in twice as many of half the width while those
+// still fit one round of 20 waves (160000, D = 121, 4 columns: 2.94 as 2 + 2,
+// 3.22).  Where no width fits one round: up to 3 columns (a matrix up to
+// 128 MB), 4 (up to 256 MB) or 8 (from HBM) a tile.  With less than five
+// waves a CU for a tile, the latency of a workgroup counts: up to 3 columns
+// and, if there are as many, three tiles (40000, D = 121, 3 columns: 1.47 as
+// 1 + 1 + 1, 1.90; 10 columns: 2.23 as 3 + 3 + 2 + 2, 2.83 as 5 + 5; 73984, 9
+// columns: 2.62 as 3 + 3 + 3, 3.15 as 5 + 4); with less than seven, up to 3
+// columns where those tiles give no more than four waves per SIMD (84100, 9
+// columns: 3.06, 3.51).
+//
+// In a form that keeps a ring of orders (`ring`: states, quasi-eigenstates,
+// conductivity) the orders stream through the cache, so a further tile costs
+// more: nine waves instead of seven, and from nine waves a tile on as few tiles
+// of up to 7 columns as possible (24 steps: 160000, D = 121, 10 columns 10.5 as
+// 5 + 5, 14.1 as 3 + 3 + 2 + 2; 122500, D = 61, 5 columns 3.30 as 3 + 2, 3.68).
+//
+// complex64, slices of 256 rows (matrices of 160 MB and more): as few tiles
+// of up to 7 columns as possible (336400, D = 121: 7 columns 7.50, as 4 + 3
+// 8.04; 8 columns 7.93 as 4 + 4, 8.19 in one), but of 6 only from HBM (409600:
+// 7.67, as 3 + 3 8.25; 266256, in the cache: 6.11 and 5.39).
+//
+// complex128: the tiles of up to 6 columns, or 7 in slices of 256 rows, whose
+// costs, fitted to 11 matrices of 2..12 columns (a matrix beyond the last-level
+// cache, or a ring, adds half a unit a tile), sum to the least and that give a CU five
+// waves, or 3.5 up to three columns (90000, D = 121,
+// 5 columns: 3.45, as 3 + 2 4.28; 10 columns: 5.96 as 5 + 5, 6.91 as
+// 3 + 3 + 2 + 2; 230400, 8 columns: 9.65 as 4 + 4, 12.35 in one; 336400, 9
+// columns: 14.8 as 5 + 4, 16.6 as 3 + 3 + 3).  A tile of 6 at a window of 832
+// takes 78 KB of LDS: 262144 rows 9.3, as 3 + 3 in 39 KB 9.9.
+int ellw_columns_per_group(bool fp64, bool ring, int Rg, int64_t window, int nr, int64_t slices,
+                           int64_t entries) {
+  if (Rg <= 1) return 1;
+  const int64_t value = std::max<int64_t>(window, 1) * (fp64 ? 16 : 8);   // LDS of a column
+  const int fit =
+      static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(8, kEllwLdsBytes / value)));
   const int64_t mb = (entries * (fp64 ? 10 : 6)) >> 20;
-  const int64_t most = mb > 256 ? 8 : nr == 256 ? 5 : mb > 128 ? 4 : 3;
-  const int cap = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(most, fit)));
-  if (Rg < 1) return 1;
-  const int tiles = (Rg + cap - 1) / cap;
-  return (Rg + tiles - 1) / tiles;
+  const double waves = static_cast<double>(slices) * (nr / 64) / 256.0;
+  auto width = [&](int tiles) { return (Rg + tiles - 1) / tiles; };
+  auto at_most = [&](int cols) { return width((Rg + cols - 1) / cols); };
+  if (fp64) {
+    constexpr double kCost[7] = {0.6, 0.8, 1.0, 1.3, 1.7, 2.05, 3.0};
+    const int most = std::min(nr == 256 ? 7 : 6, fit);
+    double best = 1e300;
+    int ct = 1;
+    for (int k = 1; k <= Rg; ++k) {
+      const int w = width(k);
+      if (w > most || (k < Rg && waves * k < (w > 3 ? 5.0 : 3.5))) continue;
+      const double c = k * (kCost[w - 1] + (ring || mb > 256 ? 0.5 : 0.0));
+      if (c < best) {
+        best = c;
+        ct = w;
+      }
+    }
+    return ct;
+  }
+  if (nr == 256) {
+    const int w = at_most(std::min(7, fit));
+    return w == 6 && mb <= 256 ? at_most(5) : w;
+  }
+  const int narrow = (Rg + std::min(3, fit) - 1) / std::min(3, fit);   // tiles of up to 3
+  if (waves < 5.0) return width(std::max(narrow, std::min(Rg, 3)));
+  if (!ring && waves < 7.0 && waves * narrow <= 16.0) return width(narrow);
+  if (ring && waves >= 9.0) return at_most(std::min(7, fit));
+  auto one_round = [&](int tiles) {
+    constexpr int kWavesPerSimd[8] = {8, 8, 8, 4, 4, 4, 3, 3};   // from the registers of CT
+    const int w = width(tiles);
+    if (w > fit) return false;
+    const int64_t lds = (w * value + 1279) / 1280 * 1280;
+    const int64_t resident =
+        std::min<int64_t>(160 * 1024 / lds * (nr / 64), 4 * kWavesPerSimd[w - 1]);
+    return waves * tiles <= (double)resident;
+  };
+  for (int k = 1; k <= Rg; ++k) {
+    const int w = width(k);
+    if (w > 7 || (w > 3 && waves * k < (ring ? 9.0 : 7.0)) || !one_round(k)) continue;
+    const bool halve = (w == 4 || w == 6) && mb <= 256 && waves * 2 * k <= 20.0 && one_round(2 * k);
+    return halve ? width(2 * k) : w;
+  }
+  return at_most(std::min(mb > 256 ? 8 : mb > 128 ? 4 : 3, fit));
 }
 
 hipError_t launch_cheb_ellw(bool fp64, bool mom, bool carry, int ct, int nr, int64_t lds_cap,
@@ -394,7 +468,7 @@ hipError_t launch_cheb_ellw(bool fp64, bool mom, bool carry, int ct, int nr, int
   const int64_t n = wg_hi - wg_lo;
   if (n <= 0) return hipSuccess;
   if (st.nlev != 1 || (carry && !mom)) return hipErrorInvalidValue;
-  if (ct < 1 || ct > 8 || (nr != 128 && nr != 256)) return hipErrorInvalidValue;
+  if (ct < 1 || ct > (fp64 ? 7 : 8) || (nr != 128 && nr != 256)) return hipErrorInvalidValue;
   // LDS: the largest staged window of the run's instances times its
   // columns (lds_cap complex values)
   const size_t lds = std::max<size_t>((size_t)(lds_cap > 0 ? lds_cap : 1) * (fp64 ? 16 : 8),
@@ -412,14 +486,17 @@ hipError_t launch_cheb_ellw(bool fp64, bool mom, bool carry, int ct, int nr, int
       case 4: CSP_ELLW(T, 4, M, CY); break; \
       case 5: CSP_ELLW(T, 5, M, CY); break; \
       case 6: CSP_ELLW(T, 6, M, CY); break; \
-      case 7: CSP_ELLW(T, 7, M, CY); break; \
-      default: CSP_ELLW(T, 8, M, CY); break; \
+      default: CSP_ELLW(T, 7, M, CY); break; \
     }                              \
   } while (0)
   if (fp64) {
     if (carry) CSP_ELLW_CT(double, true, true);
     else if (mom) CSP_ELLW_CT(double, true, false);
     else CSP_ELLW_CT(double, false, false);
+  } else if (ct == 8) {
+    if (carry) CSP_ELLW(float, 8, true, true);
+    else if (mom) CSP_ELLW(float, 8, true, false);
+    else CSP_ELLW(float, 8, false, false);
   } else {
     if (carry) CSP_ELLW_CT(float, true, true);
     else if (mom) CSP_ELLW_CT(float, true, false);
