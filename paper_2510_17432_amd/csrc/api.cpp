@@ -1263,33 +1263,9 @@ static csp_status propagate_impl(csp_context* c, const std::vector<InstIn>& ins,
     sp.push_back(make_inst(ins[g.inst].lat, g.Rg, fp64, true));
     apply_layout(sp.back(), g);
   }
-  const ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, tune ? tune->spmm_vec : 0,
-                                     tune ? tune->spmm_steps : recursion_steps(sp, fp64, c->n_cu),
-                                     tune ? tune->spmm_seg_rows : 0);
-  const int kt = sp_plan.kt;
-
-  auto fits_b = [&](int bb) {
-    // Workspace with every order of a block resident, or at least 16 of them.
-    const int need = std::min(ntr[bb - 1] + 1, 16) + kt;
-    return fixed_guess + (size_t)need * vec_bytes <= cap;
-  };
-  if (b == 0 && tune && tune->block_b > 0 && tune->block_b <= bmax && fits_b(tune->block_b)) {
-    b = tune->block_b;   // measured by csp_autotune for this shape
-    if (rep)
-      for (int k = 0; k < 8; ++k) rep->model_cost[k] = tune->model_cost_ms[k];
-  } else if (b == 0) {
-    std::vector<bool> fits(bmax + 1, false);
-    for (int bb = 1; bb <= bmax; ++bb) fits[bb] = fits_b(bb);
-    // Without a measurement: the byte model (a recursion step streams 3
-    // vectors, one (n, j) pair of the contraction about 1/32 of a vector).
-    b = select_b_rule(ntr, bmax, Nt, 3.0, 1.0 / 32.0, fits, rep ? rep->model_cost : nullptr);
-  }
-  if (Nt > 0) b = (int)std::min<int64_t>(b, Nt);
-  b = std::max(b, 1);
-  const int b_last = Nt > 0 ? (int)(Nt - (int64_t)(ceil_div(Nt, b) - 1) * b) : b;
-  const int jtiles = fp64 ? 1 : (int)ceil_div(b, 32);
-  const int N_full = ntr[b - 1];
-  const int Ktot = N_full + 1;
+  int steps = tune ? tune->spmm_steps : recursion_steps(sp, fp64, c->n_cu);
+  ChebPlan sp_plan;
+  int kt = 0, jtiles = 1, K = 0;
 
   // Chunk size: all orders of a block if they fit, else the largest multiple
   // of 16 that fits.  The ring holds K + kt slots: a launch writes kt orders
@@ -1304,19 +1280,53 @@ static csp_status propagate_impl(csp_context* c, const std::vector<InstIn>& ins,
     return by + tabs_guess;
   };
   const int wg_bound = total_wg_target + kMaxGroupCols * (int)groups.size();
-  const int kcap = fp64 ? 1 << 20 : (496 / jtiles / 16) * 16;   // LDS budget of B operands
-  int K = P.chunk_K > 0 ? P.chunk_K : Ktot;
-  if (K >= Ktot && Ktot <= kcap && ws_need(Ktot, wg_bound) <= cap) {
-    K = Ktot;
-  } else {
-    K = std::min(std::min(K, Ktot), kcap);
-    K = std::max(16, (K / 16) * 16);
-    while (K > 16 && ws_need(K, wg_bound) > cap) K -= 16;
+  const int b_in = b;
+  for (;;) {
+    sp_plan = plan_cheb(sp, fp64, false, c->n_cu, tune ? tune->spmm_vec : 0, steps,
+                        tune ? tune->spmm_seg_rows : 0);
+    kt = sp_plan.kt;
+    auto fits_b = [&](int bb) {
+      // Workspace with every order of a block resident, or at least 16 of them.
+      const int need = std::min(ntr[bb - 1] + 1, 16) + kt;
+      return fixed_guess + (size_t)need * vec_bytes <= cap;
+    };
+    b = b_in;
+    if (b == 0 && tune && tune->block_b > 0 && tune->block_b <= bmax && fits_b(tune->block_b)) {
+      b = tune->block_b;   // measured by csp_autotune for this shape
+      if (rep)
+        for (int k = 0; k < 8; ++k) rep->model_cost[k] = tune->model_cost_ms[k];
+    } else if (b == 0) {
+      std::vector<bool> fits(bmax + 1, false);
+      for (int bb = 1; bb <= bmax; ++bb) fits[bb] = fits_b(bb);
+      // Without a measurement: the byte model (a recursion step streams 3
+      // vectors, one (n, j) pair of the contraction about 1/32 of a vector).
+      b = select_b_rule(ntr, bmax, Nt, 3.0, 1.0 / 32.0, fits, rep ? rep->model_cost : nullptr);
+    }
+    if (Nt > 0) b = (int)std::min<int64_t>(b, Nt);
+    b = std::max(b, 1);
+    jtiles = fp64 ? 1 : (int)ceil_div(b, 32);
+    const int Ktot = ntr[b - 1] + 1;
+    const int kcap = fp64 ? 1 << 20 : (496 / jtiles / 16) * 16;   // LDS budget of B operands
+    K = P.chunk_K > 0 ? P.chunk_K : Ktot;
+    if (K >= Ktot && Ktot <= kcap && ws_need(Ktot, wg_bound) <= cap) {
+      K = Ktot;
+    } else {
+      K = std::min(std::min(K, Ktot), kcap);
+      K = std::max(16, (K / 16) * 16);
+      while (K > 16 && ws_need(K, wg_bound) > cap) K -= 16;
+    }
+    if (ws_need(K, wg_bound) <= cap) break;
+    // complex128: four steps where the four further slots of eight do not fit
+    // (a smaller chunk costs less than shorter launches: vectors moved per
+    // order (K + 3) / K and (kt + 2) / kt)
+    if (!(fp64 && kt > 4))
+      return fail(CSP_ENOMEM, "workspace for b=%d, K=%d exceeds the cap (%.2f GB)", b, K,
+                  cap / 1e9);
+    steps = 4;
   }
+  const int b_last = Nt > 0 ? (int)(Nt - (int64_t)(ceil_div(Nt, b) - 1) * b) : b;
   const int S = ring_slots(K);
   const int RG = ring_parts(S);    // ring parts (slot of position k: ring_slot)
-  if (ws_need(K, wg_bound) > cap)
-    return fail(CSP_ENOMEM, "workspace for b=%d, K=%d exceeds the cap (%.2f GB)", b, K, cap / 1e9);
 
   // Contraction workgroups: per group proportional to its values, an equal
   // number on each of its columns.
@@ -1739,28 +1749,34 @@ static csp_status propagate_moments_impl(csp_context* c, const std::vector<InstI
   int kt_want = tune ? tune->spmm_steps : !halving ? 4 : recursion_steps(sp, fp64, c->n_cu);
   if (carry && !cheb_carry_supported(fp64, 2, kt_want)) kt_want = 4;
   if (carry) vec_want = 2;   // the carried-state kernels hold 2 values per lane
-  const ChebPlan sp_plan = plan_cheb(sp, fp64, true, c->n_cu, vec_want, kt_want,
-                                     tune ? tune->spmm_seg_rows : 0);
-  const int kt = sp_plan.kt;
   const int P_batch = 16;
-
-  // Workspace.
-  size_t need = 0;
-  const size_t part_bytes = (size_t)P_batch * kt * sp_plan.total_items * 8 * sizeof(double);
-  need += align256(part_bytes);
-  for (auto& g : groups) {
-    need += align256(4 * g.stride() * csz) + align256(g.M * csz);   // ring + psi0
-    if (carry) need += 2 * align256(g.M * csz);                      // carry in / out
-    need += align256((size_t)(steps_max + 1) * 4 * g.Rg * 16);       // dots
-    need += align256((size_t)(Nk_max + 1) * g.Rg * 16);              // mu
-  }
-  need += align256(sizeof(ChebInst) * groups.size()) + align256(sizeof(MomInst) * groups.size()) +
-          align256(sizeof(MomCorrInst) * groups.size()) +
-          align256(sizeof(double) * 256 * kMaxGroupCols) + align256(2 * sizeof(int));
   size_t cap = 0;
   CHECK(memory_cap(c, P.mem_cap_bytes, &cap));
-  if (need > cap)
-    return fail(CSP_ENOMEM, "workspace %.2f GB exceeds the cap %.2f GB", need / 1e9, cap / 1e9);
+
+  // Workspace.
+  ChebPlan sp_plan;
+  size_t need = 0, part_bytes = 0;
+  for (;;) {
+    sp_plan = plan_cheb(sp, fp64, true, c->n_cu, vec_want, kt_want, tune ? tune->spmm_seg_rows : 0);
+    part_bytes = (size_t)P_batch * sp_plan.kt * sp_plan.total_items * 8 * sizeof(double);
+    need = align256(part_bytes);
+    for (auto& g : groups) {
+      need += align256(4 * g.stride() * csz) + align256(g.M * csz);   // ring + psi0
+      if (carry) need += 2 * align256(g.M * csz);                      // carry in / out
+      need += align256((size_t)(steps_max + 1) * 4 * g.Rg * 16);       // dots
+      need += align256((size_t)(Nk_max + 1) * g.Rg * 16);              // mu
+    }
+    need += align256(sizeof(ChebInst) * groups.size()) +
+            align256(sizeof(MomInst) * groups.size()) +
+            align256(sizeof(MomCorrInst) * groups.size()) +
+            align256(sizeof(double) * 256 * kMaxGroupCols) + align256(2 * sizeof(int));
+    if (need <= cap) break;
+    // complex128: four steps where the records of eight do not fit
+    if (!(fp64 && sp_plan.kt > 4))
+      return fail(CSP_ENOMEM, "workspace %.2f GB exceeds the cap %.2f GB", need / 1e9, cap / 1e9);
+    kt_want = 4;
+  }
+  const int kt = sp_plan.kt;
   CHECK(ws_reserve(c, need));
   Carver cv(c->ws);
   double* d_part = (double*)cv.take(part_bytes);
@@ -2281,32 +2297,42 @@ csp_status qe_state_based(csp_context* c, const csp_lattice* L, const void* dev_
   std::vector<ChebInst> sp;
   for (auto& g : groups)
     for (int d = 0; d < 2; ++d) sp.push_back(make_inst(L, g.Rg, fp64, true));
-  const ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, recursion_steps(sp, fp64, c->n_cu), 0);
-  const int kt = sp_plan.kt;
+  ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, recursion_steps(sp, fp64, c->n_cu), 0);
   int B64 = 1;
   while (B64 < rows) B64 *= 2;
   const int kcap = fp64 ? (int)((60 * 1024) / (sizeof(double2) * B64)) / 16 * 16 : 240;
   size_t cap = 0;
   CHECK(memory_cap(c, P.mem_cap_bytes, &cap));
-  auto ws_need = [&](int K_) {
+  auto ws_need = [&](int K_, int kt_) {
     size_t by = 0;
     for (auto& g : groups)
-      by += 2 * (align256((size_t)(K_ + kt) * g.stride() * csz) + align256(g.M * csz) +
+      by += 2 * (align256((size_t)(K_ + kt_) * g.stride() * csz) + align256(g.M * csz) +
                  align256((size_t)nE * g.M * csz));
     by += fp64 ? align256(sizeof(double2) * (size_t)K_ * B64)
                : align256((size_t)64 * 64 * ceil_div(K_, 16));
     by += align256(sizeof(ChebInst) * sp.size()) + align256(sizeof(QeInst) * sp.size());
     return by;
   };
-  int K = std::min(NkMax + 1, kcap);
-  if (K < NkMax + 1) K = std::max(16, K / 16 * 16);
-  while (K > 16 && ws_need(K) > cap) K = (K > 32 ? (K - 1) / 16 * 16 : 16);
-  if (ws_need(K) > cap)
+  auto chunk = [&](int kt_) {
+    int K_ = std::min(NkMax + 1, kcap);
+    if (K_ < NkMax + 1) K_ = std::max(16, K_ / 16 * 16);
+    while (K_ > 16 && ws_need(K_, kt_) > cap) K_ = (K_ > 32 ? (K_ - 1) / 16 * 16 : 16);
+    return K_;
+  };
+  int K = chunk(sp_plan.kt);
+  // four steps where the further slots of eight would take orders of the chunk
+  // (every chunk reads and writes the accumulators) or do not fit
+  if (fp64 && sp_plan.kt > 4 && (chunk(4) > K || ws_need(K, sp_plan.kt) > cap)) {
+    sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, 4, 0);
+    K = chunk(4);
+  }
+  const int kt = sp_plan.kt;
+  if (ws_need(K, kt) > cap)
     return fail(CSP_ENOMEM, "quasi-eigenstate workspace %.2f GB exceeds the cap %.2f GB",
-                ws_need(K) / 1e9, cap / 1e9);
+                ws_need(K, kt) / 1e9, cap / 1e9);
   const int S = K + kt;
   const int RG = ring_parts(S);    // ring parts (slot of position k: ring_slot)
-  CHECK(ws_reserve(c, ws_need(K)));
+  CHECK(ws_reserve(c, ws_need(K, kt)));
   Carver cv(c->ws);
   std::vector<void*> carry(sp.size()), acc(sp.size()), slots(sp.size());
   for (size_t i = 0; i < sp.size(); ++i) {
@@ -2533,8 +2559,7 @@ extern "C" csp_status csp_quasi_eigenstates(csp_context* c, const csp_lattice* L
   }
   std::vector<ChebInst> sp;
   for (auto& g : groups) sp.push_back(make_inst(L, g.Rg, fp64, true));
-  const ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, recursion_steps(sp, fp64, c->n_cu), 0);
-  const int kt = sp_plan.kt;
+  ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, recursion_steps(sp, fp64, c->n_cu), 0);
 
   // Orders per contraction chunk: all of them when they fit, else a multiple
   // of 16 (LDS holds the chunk's coefficients of one energy tile; the ring
@@ -2545,25 +2570,36 @@ extern "C" csp_status csp_quasi_eigenstates(csp_context* c, const csp_lattice* L
   const int kcap = fp64 ? (int)((60 * 1024) / (sizeof(double2) * B64)) / 16 * 16 : 496;
   size_t cap = 0;
   CHECK(memory_cap(c, P.mem_cap_bytes, &cap));
-  auto ws_need = [&](int K_) {
+  auto ws_need = [&](int K_, int kt_) {
     size_t by = 0;
     for (auto& g : groups)
-      by += align256((size_t)(K_ + kt) * g.stride() * csz) + align256(g.M * csz) +
+      by += align256((size_t)(K_ + kt_) * g.stride() * csz) + align256(g.M * csz) +
             align256((size_t)nE * g.M * csz);
     by += fp64 ? align256(sizeof(double2) * (size_t)K_ * B64 * n_et)
                : align256(bop_bytes(1, K_) * n_et) + align256(sizeof(float) * 16 * ceil_div(K_, 16));
     by += align256(sizeof(ChebInst) * groups.size()) + align256(sizeof(QeInst) * groups.size());
     return by;
   };
-  int K = std::min(Nmax + 1, kcap);
-  if (K < Nmax + 1) K = std::max(16, K / 16 * 16);
-  while (K > 16 && ws_need(K) > cap) K = (K > 32 ? (K - 1) / 16 * 16 : 16);
-  if (ws_need(K) > cap)
+  auto chunk = [&](int kt_) {
+    int K_ = std::min(Nmax + 1, kcap);
+    if (K_ < Nmax + 1) K_ = std::max(16, K_ / 16 * 16);
+    while (K_ > 16 && ws_need(K_, kt_) > cap) K_ = (K_ > 32 ? (K_ - 1) / 16 * 16 : 16);
+    return K_;
+  };
+  int K = chunk(sp_plan.kt);
+  // four steps where the further slots of eight would take orders of the chunk
+  // (every chunk reads and writes the accumulators) or do not fit
+  if (fp64 && sp_plan.kt > 4 && (chunk(4) > K || ws_need(K, sp_plan.kt) > cap)) {
+    sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, 4, 0);
+    K = chunk(4);
+  }
+  const int kt = sp_plan.kt;
+  if (ws_need(K, kt) > cap)
     return fail(CSP_ENOMEM, "quasi-eigenstate workspace %.2f GB exceeds the cap %.2f GB",
-                ws_need(K) / 1e9, cap / 1e9);
+                ws_need(K, kt) / 1e9, cap / 1e9);
   const int S = K + kt;
   const int RG = ring_parts(S);    // ring parts (slot of position k: ring_slot)
-  CHECK(ws_reserve(c, ws_need(K)));
+  CHECK(ws_reserve(c, ws_need(K, kt)));
   Carver cv(c->ws);
   std::vector<void*> outs(groups.size());
   for (size_t gi = 0; gi < groups.size(); ++gi) {
@@ -2791,33 +2827,43 @@ extern "C" csp_status csp_ec_correlation(csp_context* c, const csp_lattice* L, i
   }
   std::vector<ChebInst> sp;
   for (auto& g : groups) sp.push_back(make_inst(L, g.Rg, fp64, true));
-  const ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, recursion_steps(sp, fp64, c->n_cu), 0);
-  const int kt = sp_plan.kt;
+  ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, recursion_steps(sp, fp64, c->n_cu), 0);
   const int64_t target_slices = std::max<int64_t>(1, (int64_t)c->n_cu * 4 / R);
   const int64_t slice_len = std::max<int64_t>(512, (ceil_div(N, target_slices) + 7) / 8 * 8);
   const int n_slices = (int)ceil_div(N, slice_len);
   const size_t psz = fp64 ? sizeof(double2) : sizeof(float2);   // partial element
 
-  int K = std::min(Nmax + 1, 128);
   size_t cap = 0;
   CHECK(memory_cap(c, P.mem_cap_bytes, &cap));
-  auto ws_need = [&](int K_) {
+  auto ws_need = [&](int K_, int kt_) {
     size_t by = 0;
     for (auto& g : groups)
-      by += align256((size_t)(K_ + kt) * g.stride() * csz) + 2 * align256(g.M * csz) +
+      by += align256((size_t)(K_ + kt_) * g.stride() * csz) + 2 * align256(g.M * csz) +
             2 * align256((size_t)nE * g.M * csz) +
             align256((size_t)g.Rg * n_slices * K_ * ldp * psz);
     by += align256(sizeof(ChebInst) * groups.size()) + align256(sizeof(EcInst) * groups.size()) +
           align256(sizeof(MomCorrInst));
     return by;
   };
-  while (K > 16 && ws_need(K) > cap) K = std::max(16, K - 16);
-  if (ws_need(K) > cap)
+  auto chunk = [&](int kt_) {
+    int K_ = std::min(Nmax + 1, 128);
+    while (K_ > 16 && ws_need(K_, kt_) > cap) K_ = std::max(16, K_ - 16);
+    return K_;
+  };
+  int K = chunk(sp_plan.kt);
+  // four steps where the further slots of eight would take orders of the chunk
+  // (every chunk reads the bras) or do not fit
+  if (fp64 && sp_plan.kt > 4 && (chunk(4) > K || ws_need(K, sp_plan.kt) > cap)) {
+    sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, 4, 0);
+    K = chunk(4);
+  }
+  const int kt = sp_plan.kt;
+  if (ws_need(K, kt) > cap)
     return fail(CSP_ENOMEM, "conductivity workspace %.2f GB exceeds the cap %.2f GB",
-                ws_need(K) / 1e9, cap / 1e9);
+                ws_need(K, kt) / 1e9, cap / 1e9);
   const int S = K + kt;
   const int RG = ring_parts(S);    // ring parts (slot of position k: ring_slot)
-  CHECK(ws_reserve(c, ws_need(K)));
+  CHECK(ws_reserve(c, ws_need(K, kt)));
   Carver cv(c->ws);
   std::vector<void*> jpsi(groups.size()), qeg(groups.size()), bra(groups.size()),
       part(groups.size());
@@ -3104,7 +3150,7 @@ extern "C" csp_status csp_autotune(csp_context* c, int32_t n_inst, const csp_lat
 
   // recursion candidates (values per lane, steps per launch, rows per work
   // item) and the largest record buffer among them
-  struct Cand { int vec, kt, seg; };
+  struct Cand { int vec, kt, seg; int64_t rec; };
   std::vector<Cand> cands;
   int64_t max_rec = 0;
   bool any_sparse = false;
@@ -3117,7 +3163,7 @@ extern "C" csp_status csp_autotune(csp_context* c, int32_t n_inst, const csp_lat
         std::vector<ChebInst> tmp_sp = sp;
         ChebPlan p = plan_cheb(tmp_sp, fp64, mom, c->n_cu, v, kt, seg);
         if (p.total_items < 1 || ceil_div(p.total_items, 4) > INT32_MAX) continue;
-        cands.push_back({v, kt, seg});
+        cands.push_back({v, kt, seg, p.total_items * kt});
         max_rec = std::max(max_rec, p.total_items * kt);
       }
     }
@@ -3162,6 +3208,12 @@ extern "C" csp_status csp_autotune(csp_context* c, int32_t n_inst, const csp_lat
   int K_t = (mom || P.mode == CSP_FP64_SEQ) ? 10 : 32;
   while (K_t > 16 && tune_ws(K_t) > cap) K_t -= 16;
   if (K_t > 10 && tune_ws(K_t) > cap) K_t = 10;
+  if (fp64 && mom && tune_ws(K_t) > cap) {   // without the records of eight steps
+    cands.erase(std::remove_if(cands.begin(), cands.end(), [](const Cand& q) { return q.kt > 4; }),
+                cands.end());
+    max_rec = 0;
+    for (auto& q : cands) max_rec = std::max(max_rec, q.rec);
+  }
   if (tune_ws(K_t) > cap)
     return fail(CSP_ENOMEM, "autotuner workspace %.2f GB exceeds the cap %.2f GB", tune_ws(K_t) / 1e9,
                 cap / 1e9);
