@@ -451,8 +451,12 @@ csp_status csp_dos_noalloc(csp_context *ctx, const double *dev_corr, int64_t Nt,
  * result is cached in the context under the instances' shape (lattice
  * kinds and sizes, column groups, precision, assembly); csp_propagate and
  * csp_propagate_batch use a cached entry for their shape: its launch shapes
- * always, its b when params->block_b is 0.  The states and correlation
- * buffers of the caller are not touched (the timing uses workspace). */
+ * (in complex128 four steps per launch for eight whose workspace exceeds the
+ * cap), its b when params->block_b is 0.  The sequential mode of chain, square
+ * and honeycomb lattices chooses its own shapes unless it replays a graph: its
+ * recursion also accumulates the propagated state, which no candidate does.
+ * The states and correlation buffers of the caller are not touched (the timing
+ * uses workspace). */
 csp_status csp_autotune(csp_context *ctx, int32_t n_inst, const csp_lattice *const *lats,
                         const int32_t *R, const csp_params *params, csp_tuning *out);
 

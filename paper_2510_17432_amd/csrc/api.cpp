@@ -2052,10 +2052,9 @@ static csp_status propagate_seq_impl(csp_context* c, const std::vector<InstIn>& 
     sp.push_back(make_inst(ins[g.inst].lat, g.Rg, true, true));
     apply_layout(sp.back(), g);
   }
-  const csp_tuning* tune = find_tuning(c, ins, true, CSP_ASSEMBLE_STATES);
+  // (a tuning record holds shapes of the ring's kernel at 1 to 8 steps: not used)
   const int kt = kSeqSteps;
-  const ChebPlan plan = plan_cheb(sp, true, false, c->n_cu, 2, kt, tune ? tune->spmm_seg_rows : 0,
-                                  true);
+  const ChebPlan plan = plan_cheb(sp, true, false, c->n_cu, 2, kt, 0, true);
   constexpr int kRecSlots = 16;      // time steps whose records wait for one sum
 
   // Workspace: four slots, psi0 and two carried states per group.
