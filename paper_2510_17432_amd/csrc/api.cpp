@@ -1096,22 +1096,86 @@ static bool seq_form(const csp_context* c, const std::vector<InstIn>& ins, const
   return !wide_ribbons(insts, 2, c->n_cu);
 }
 
+// Column groups of a propagation (explicit matrices: of any size).
+static std::vector<Group> column_groups(const std::vector<InstIn>& ins) {
+  std::vector<Group> groups;
+  for (size_t i = 0; i < ins.size(); ++i) {
+    int col = ins[i].col_base;
+    for (int Rg : split_columns(ins[i].R, ins[i].lat->g.kind == CSP_SPARSE)) {
+      Group g;
+      g.inst = (int)i;
+      g.col0 = col;
+      g.Rg = Rg;
+      set_layout(g, ins[i].lat);
+      groups.push_back(g);
+      col += Rg;
+    }
+  }
+  return groups;
+}
+
+constexpr size_t kTabsGuess = 64u << 20;   // coefficient tables and instance tables
+constexpr int kSeqRecSlots = 16;           // time steps whose records wait for one sum
+constexpr size_t kSelfDotWgs = 256;        // self-dot partial blocks
+
+// Workspace of the state form with a ring of `slots` orders and blocks of b
+// steps: ring, psi0 and carried state, partial sums of n_wg workgroups, tables.
+static size_t ring_workspace(const std::vector<Group>& groups, size_t csz, int slots, int b,
+                             int n_wg) {
+  size_t by = kTabsGuess + align256((size_t)n_wg * b * 16) * 2;
+  for (auto& g : groups)
+    by += align256((size_t)slots * g.stride() * csz) + 2 * align256(g.M * csz);
+  return by;
+}
+
+// Workspace of the sequential form: four slots, psi0 and two carried states per
+// group, the records of the step sums and tables.
+static size_t seq_workspace(const std::vector<Group>& groups, const ChebPlan& plan) {
+  size_t by = align256((size_t)kSeqRecSlots * plan.total_items * sizeof(double2)) +
+              align256(sizeof(double) * kSelfDotWgs * kMaxGroupCols) + align256(2 * sizeof(int)) +
+              2 * align256(sizeof(ChebInst) * groups.size()) +
+              align256(sizeof(SeqInst) * groups.size());
+  for (auto& g : groups)
+    by += align256(4 * g.stride() * sizeof(double2)) + 3 * align256(g.M * sizeof(double2));
+  return by;
+}
+
 // Column windows.  Every column is propagated independently, so when even
-// the smallest workspace (a 16-order chunk plus psi0 and carry for the
-// state assembly, 3 vectors plus psi0 and two carries for the moment
-// assembly) of all columns exceeds the memory cap, the columns are run in
-// passes over windows of at most w columns (w a power of two) per instance.
+// the smallest workspace of all columns exceeds the memory cap, the columns are
+// run in passes over windows of at most w columns (w a power of two) per
+// instance.  The smallest workspace: a 16-order chunk with the steps of a
+// launch (at least what complex128 falls back to), psi0 and carry for the state
+// assembly; the sequential form's own; 6 vectors and 96 MB for the moment
+// assembly.
 static csp_status plan_passes(csp_context* c, const std::vector<InstIn>& ins, const csp_params& P,
-                              std::vector<std::vector<InstIn>>* passes) {
-  const size_t csz = P.mode == CSP_FP32_CONC ? sizeof(float2) : sizeof(double2);
-  const double slots = P.assembly == CSP_ASSEMBLE_MOMENTS ? 6.0 : 18.0;
+                              bool batch_call, std::vector<std::vector<InstIn>>* passes) {
+  const bool fp64 = P.mode != CSP_FP32_CONC;
+  const size_t csz = fp64 ? sizeof(double2) : sizeof(float2);
   size_t cap_b = 0;
   CHECK(memory_cap(c, P.mem_cap_bytes, &cap_b));
   const double cap = (double)cap_b;
   auto need = [&](const std::vector<InstIn>& v) {
-    double vb = 0;
-    for (auto& in : v) vb += (double)in.lat->g.N * in.R * csz;
-    return vb * slots + (double)(96u << 20);
+    if (P.assembly == CSP_ASSEMBLE_MOMENTS) {
+      double vb = 0;
+      for (auto& in : v) vb += (double)in.lat->g.N * in.R * csz;
+      return vb * 6.0 + (double)(96u << 20);
+    }
+    const std::vector<Group> groups = column_groups(v);
+    std::vector<ChebInst> sp;
+    for (auto& g : groups) sp.push_back(make_inst(v[g.inst].lat, g.Rg, fp64, true));
+    if (seq_form(c, v, P, batch_call)) {
+      const ChebPlan plan = plan_cheb(sp, true, false, c->n_cu, 2, kSeqSteps, 0, true);
+      return (double)seq_workspace(groups, plan);
+    }
+    const csp_tuning* tune = find_tuning(c, v, fp64, CSP_ASSEMBLE_STATES);
+    int kt = tune ? tune->spmm_steps : recursion_steps(sp, fp64, c->n_cu);
+    if (fp64) kt = std::min(kt, 4);
+    kt = plan_cheb(sp, fp64, false, c->n_cu, tune ? tune->spmm_vec : 0, kt).kt;
+    const int b = P.mode == CSP_FP64_SEQ ? 1 : P.block_b > 0 ? P.block_b
+                                         : fp64 ? kMaxFp64B : 32 * kMaxJTiles;
+    const int n_wg = c->n_cu * (tune ? tune->contract_wg_per_cu : 4) +
+                     kMaxGroupCols * (int)groups.size();
+    return (double)ring_workspace(groups, csz, 16 + kt, b, n_wg);
   };
   passes->clear();
   if (need(ins) <= cap) {
@@ -1160,7 +1224,7 @@ static csp_status propagate_impl(csp_context* c, const std::vector<InstIn>& ins,
     std::vector<std::vector<InstIn>> passes;
     {
       DeviceGuard dg0(c->device);
-      CHECK(plan_passes(c, ins, P, &passes));
+      CHECK(plan_passes(c, ins, P, batch_call, &passes));
     }
     if (passes.size() > 1) {
       csp_report tot{};
@@ -1233,29 +1297,19 @@ static csp_status propagate_impl(csp_context* c, const std::vector<InstIn>& ins,
     if (ntr[j] < 1) return fail(CSP_ENUMERIC, "no truncation order for x = %g", (j + 1) * P.tau_tilde);
 
   // ---------------------------------------------------------- groups & memory
-  std::vector<Group> groups;
+  std::vector<Group> groups = column_groups(ins);
   int64_t vec_elems = 0;   // complex values of one vector over all groups (rows padded)
   int64_t vec_alg = 0;     // the same without the padding (algorithmic bytes)
-  for (size_t i = 0; i < ins.size(); ++i) {
-    int col = ins[i].col_base;
-    for (int Rg : split_columns(ins[i].R, ins[i].lat->g.kind == CSP_SPARSE)) {
-      Group g;
-      g.inst = (int)i;
-      g.col0 = col;
-      g.Rg = Rg;
-      set_layout(g, ins[i].lat);
-      groups.push_back(g);
-      vec_elems += g.M;
-      vec_alg += ins[i].lat->g.N * Rg;
-      col += Rg;
-    }
+  for (auto& g : groups) {
+    vec_elems += g.M;
+    vec_alg += ins[g.inst].lat->g.N * g.Rg;
   }
   size_t cap = 0;
   CHECK(memory_cap(c, P.mem_cap_bytes, &cap));
   const size_t vec_bytes = (size_t)vec_elems * csz + 256 * groups.size();
   const csp_tuning* tune = find_tuning(c, ins, fp64, CSP_ASSEMBLE_STATES);
   const int total_wg_target = c->n_cu * (tune ? tune->contract_wg_per_cu : 4);
-  const size_t fixed_guess = 2 * vec_bytes + (size_t)total_wg_target * 64 * 16 + (64u << 20);
+  const size_t fixed_guess = 2 * vec_bytes + (size_t)total_wg_target * 64 * 16 + kTabsGuess;
 
   // recursion launch shape (steps per launch kt)
   std::vector<ChebInst> sp;
@@ -1270,14 +1324,9 @@ static csp_status propagate_impl(csp_context* c, const std::vector<InstIn>& ins,
   // Chunk size: all orders of a block if they fit, else the largest multiple
   // of 16 that fits.  The ring holds K + kt slots: a launch writes kt orders
   // past the newest one while the chunk in progress must stay intact.
-  const size_t tabs_guess = (64u << 20);
   auto ring_slots = [&](int K_) { return std::max(K_ + kt, kt + 2); };
-  auto ws_need = [&](int K_, int n_wg_total) {
-    size_t by = 0;
-    for (auto& g : groups)
-      by += align256((size_t)ring_slots(K_) * g.stride() * csz) + 2 * align256(g.M * csz);
-    by += align256((size_t)n_wg_total * b * 16) * 2;
-    return by + tabs_guess;
+  auto ws_need = [&](int K_, int n_wg) {
+    return ring_workspace(groups, csz, ring_slots(K_), b, n_wg);
   };
   const int wg_bound = total_wg_target + kMaxGroupCols * (int)groups.size();
   const int b_in = b;
@@ -1367,7 +1416,7 @@ static csp_status propagate_impl(csp_context* c, const std::vector<InstIn>& ins,
     need += align256((size_t)S * g.stride() * csz) + 2 * align256(g.M * csz);
     need += align256((size_t)g.n_wg * b * 16);
   }
-  const size_t n_sd = 256;   // self-dot partial blocks
+  const size_t n_sd = kSelfDotWgs;
   need += align256(sizeof(double) * n_sd * kMaxGroupCols);
   need += align256(2 * sizeof(int)) + align256(2 * sizeof(int64_t));
   need += align256(sizeof(ChebInst) * groups.size()) + align256(sizeof(ContractInst) * groups.size()) +
@@ -1720,22 +1769,12 @@ static csp_status propagate_moments_impl(csp_context* c, const std::vector<InstI
   const int steps_max = halving ? (Nk_max + 1) / 2 : Nk_max;
 
   // Column groups (powers of two, <= 32 columns).
-  std::vector<Group> groups;
+  std::vector<Group> groups = column_groups(ins);
   int64_t vec_alg = 0;     // complex values of one vector over all groups (unpadded)
   int rmax = 1;
-  for (size_t i = 0; i < ins.size(); ++i) {
-    int col = ins[i].col_base;
-    for (int Rg : split_columns(ins[i].R, ins[i].lat->g.kind == CSP_SPARSE)) {
-      Group g;
-      g.inst = (int)i;
-      g.col0 = col;
-      g.Rg = Rg;
-      set_layout(g, ins[i].lat);
-      groups.push_back(g);
-      vec_alg += ins[i].lat->g.N * Rg;
-      rmax = std::max(rmax, Rg);
-      col += Rg;
-    }
+  for (auto& g : groups) {
+    vec_alg += ins[g.inst].lat->g.N * g.Rg;
+    rmax = std::max(rmax, g.Rg);
   }
   std::vector<ChebInst> sp;
   for (auto& g : groups) {
@@ -2030,22 +2069,12 @@ static csp_status propagate_seq_impl(csp_context* c, const std::vector<InstIn>& 
   HIPCALL(hipStreamSynchronize(s));
   if (Nk < 1) return fail(CSP_ENUMERIC, "no truncation order for x = %g", P.tau_tilde);
 
-  std::vector<Group> groups;
+  std::vector<Group> groups = column_groups(ins);
   int64_t vec_alg = 0;
   int rmax = 1;
-  for (size_t i = 0; i < ins.size(); ++i) {
-    int col = ins[i].col_base;
-    for (int Rg : split_columns(ins[i].R)) {
-      Group g;
-      g.inst = (int)i;
-      g.col0 = col;
-      g.Rg = Rg;
-      set_layout(g, ins[i].lat);
-      groups.push_back(g);
-      vec_alg += ins[i].lat->g.N * Rg;
-      rmax = std::max(rmax, Rg);
-      col += Rg;
-    }
+  for (auto& g : groups) {
+    vec_alg += ins[g.inst].lat->g.N * g.Rg;
+    rmax = std::max(rmax, g.Rg);
   }
   std::vector<ChebInst> sp;
   for (auto& g : groups) {
@@ -2055,15 +2084,10 @@ static csp_status propagate_seq_impl(csp_context* c, const std::vector<InstIn>& 
   // (a tuning record holds shapes of the ring's kernel at 1 to 8 steps: not used)
   const int kt = kSeqSteps;
   const ChebPlan plan = plan_cheb(sp, true, false, c->n_cu, 2, kt, 0, true);
-  constexpr int kRecSlots = 16;      // time steps whose records wait for one sum
 
-  // Workspace: four slots, psi0 and two carried states per group.
-  const size_t n_sd = 256;
-  const size_t rec_bytes = (size_t)kRecSlots * plan.total_items * sizeof(double2);
-  size_t need = align256(rec_bytes) + align256(sizeof(double) * n_sd * kMaxGroupCols) +
-                align256(2 * sizeof(int)) + 2 * align256(sizeof(ChebInst) * groups.size()) +
-                align256(sizeof(SeqInst) * groups.size());
-  for (auto& g : groups) need += align256(4 * g.stride() * csz) + 3 * align256(g.M * csz);
+  const size_t n_sd = kSelfDotWgs;
+  const size_t rec_bytes = (size_t)kSeqRecSlots * plan.total_items * sizeof(double2);
+  const size_t need = seq_workspace(groups, plan);
   size_t cap = 0;
   CHECK(memory_cap(c, P.mem_cap_bytes, &cap));
   if (need > cap)
@@ -2183,7 +2207,7 @@ static csp_status propagate_seq_impl(csp_context* c, const std::vector<InstIn>& 
       CHECK(prof.end(ev));
     }
     ++slots;
-    if (slots == kRecSlots || j + 1 == Nt || P.check_norm) {
+    if (slots == kSeqRecSlots || j + 1 == Nt || P.check_norm) {
       HIPCALL(launch_seq_corr(d_si, (int)si.size(), rmax, slots, d_rec, plan.total_items,
                               j + 1 - slots, s));
       slots = 0;

@@ -1,7 +1,8 @@
 """GPU: complex128 calls whose cap holds the workspace of four steps per launch
 but not that of eight (a ring of 16 orders and eight more slots): they run
 with four steps, or keep the chunk that four steps leave, with the results of
-an uncapped call.  Sums over other chunks and rows, in FP64: 1e-12 of values
+an uncapped call; and column windows of calls whose smallest workspace does not
+fit for all columns at once.  Sums over other chunks and rows, in FP64: 1e-12 of values
 of order one (correlations), of |psi|^2 = 1 (moments) and of the largest
 element (quasi-eigenstates)."""
 import numpy as np
@@ -100,3 +101,24 @@ def test_conductivity_in_four_steps(csp, ctx):
         Nt, mode="fp64_conc", mem_cap_bytes=34 * VEC))
     assert rep.spmm_steps == 4 and rep.chunk_K == 16
     assert (got - ref).abs().max().item() < 1e-12 * ref.abs().max().item()
+
+
+@pytest.mark.parametrize("mode,slots,slack,passes,steps", [
+    # two columns, one vector of both = 2 columns: 16 + kt slots, psi0, carry and
+    # 66 MB of tables; complex64 at 8 steps 52 column vectors, complex128 at 4
+    # steps 44, the sequential form 14 with neither tables nor a ring
+    ("fp32_conc", 44, 98, 2, 8), ("fp64_conc", 40, 98, 2, 8), ("fp64_conc", 45, 67, 1, 4),
+    ("fp64_seq", 20, 0, 1, 7), ("fp64_seq", 10, 0, 2, 7)])
+def test_windows_by_the_real_need(csp, ctx, mode, slots, slack, passes, steps):
+    print("[gpu] windows %s %d" % (mode, slots), flush=True)
+    g, psi, Nt = lattice(csp, ctx), state(2), 6
+    if mode == "fp32_conc":
+        psi = psi.to(torch.complex64)
+    ref, rep = csp.csp_propagate(ctx, g, psi, csp.make_params(Nt, mode=mode))
+    assert rep.n_passes == 1
+    cap = slots * (VEC // 2 if mode == "fp32_conc" else VEC) + slack * MB
+    ctx.trim()
+    got, rep = csp.csp_propagate(ctx, g, psi, csp.make_params(Nt, mode=mode, mem_cap_bytes=cap))
+    assert rep.n_passes == passes and rep.spmm_steps == steps
+    assert rep.workspace_bytes <= cap
+    assert (got - ref).abs().max().item() < (2e-5 if mode == "fp32_conc" else 1e-12)
