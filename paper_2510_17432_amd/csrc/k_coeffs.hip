@@ -86,18 +86,19 @@ __device__ __forceinline__ int bes_rows(double (&tile)[2][kBesLanes][kBesTile + 
         t[lane][kBesTile - 1] = r.cur * inv;   // order 0, at 16 g + 16
       } else {
         if (g == gM) r.cur = seed;
-        // orders stored before a rescaling take the ones still to come
-        double sc = 0.0;
+        // orders stored before a rescaling take the ones still to come (the
+        // power of two first: it underflows only with the coefficient)
+        int e = 0;
         auto store = [&](int i) {
-          if (i % EVERY == 0) sc = ldexp(inv2, 600 * (r.scaled - total));
-          t[lane][i - 1] = r.cur * sc;
+          if (i % EVERY == 0) e = 600 * (r.scaled - total);
+          return t[lane][i - 1] = ldexp(r.cur, e) * inv2;
         };
         if (kBesTile * g + kBesTile >= search_from) {
           // truncation: the smallest order above x with |c_n| <= eta
           bes_group<EVERY>(r, inv_x, [&](int i) {
-            store(i);
+            const double v = store(i);
             const int k = kBesTile * g + i;
-            if (k >= first_above && fabs(r.cur * sc) <= eta) N = k;
+            if (k >= first_above && fabs(v) <= eta) N = k;
           });
         } else {
           bes_group<EVERY>(r, inv_x, store);
