@@ -64,10 +64,16 @@ __global__ __launch_bounds__(256) void k_mom_corr(const MomCorrInst* __restrict_
   const int Rg = M.Rg;
   if (j0 >= bk || r0 >= Rg) return;
   const double2* mu = reinterpret_cast<const double2*>(M.mu);
-  int nt[kMcT], nmax = 0;
+  // truncation orders of the four times (the last time again past the block's
+  // end) and their rows of the table
+  int nt[kMcT], nmin = INT32_MAX, nmax = 0;
+  const double* row[kMcT];
 #pragma unroll
   for (int q = 0; q < kMcT; ++q) {
-    nt[q] = j0 + q < bk ? ntr[j0 + q] : -1;
+    const int j = j0 + q < bk ? j0 + q : bk - 1;
+    nt[q] = ntr[j];
+    row[q] = a + (int64_t)j * lda;
+    nmin = min(nmin, nt[q]);
     nmax = max(nmax, nt[q]);
   }
   double sx[kMcT][kMcC], sy[kMcT][kMcC];
@@ -75,20 +81,39 @@ __global__ __launch_bounds__(256) void k_mom_corr(const MomCorrInst* __restrict_
   for (int q = 0; q < kMcT; ++q)
 #pragma unroll
     for (int c = 0; c < kMcC; ++c) sx[q][c] = sy[q][c] = 0.0;
+  auto moment = [&](int n, int c) {
+    return r0 + c < Rg ? mu[(int64_t)n * Rg + r0 + c] : make_double2(0.0, 0.0);
+  };
+  int n = lane;
 #pragma unroll 2
-  for (int n = lane; n <= nmax; n += 64) {
+  for (; n <= nmin; n += 64) {
     double w[kMcT];
 #pragma unroll
-    for (int q = 0; q < kMcT; ++q) w[q] = n <= nt[q] ? a[(int64_t)(j0 + q) * lda + n] : 0.0;
+    for (int q = 0; q < kMcT; ++q) w[q] = row[q][n];
 #pragma unroll
     for (int c = 0; c < kMcC; ++c) {
-      const double2 m = r0 + c < Rg ? mu[(int64_t)n * Rg + r0 + c] : make_double2(0.0, 0.0);
+      const double2 m = moment(n, c);
 #pragma unroll
       for (int q = 0; q < kMcT; ++q) {
         sx[q][c] = fma(w[q], m.x, sx[q][c]);
         sy[q][c] = fma(w[q], m.y, sy[q][c]);
       }
     }
+  }
+  // orders past a time's truncation are no part of its sum, whatever their
+  // moments (with |H| below the spectrum they grow past the largest number)
+  for (; n <= nmax; n += 64) {
+#pragma unroll
+    for (int q = 0; q < kMcT; ++q)
+      if (n <= nt[q]) {
+        const double w = row[q][n];
+#pragma unroll
+        for (int c = 0; c < kMcC; ++c) {
+          const double2 m = moment(n, c);
+          sx[q][c] = fma(w, m.x, sx[q][c]);
+          sy[q][c] = fma(w, m.y, sy[q][c]);
+        }
+      }
   }
   double2* corr = reinterpret_cast<double2*>(M.corr);
 #pragma unroll
