@@ -56,11 +56,12 @@ constexpr int kMcT = 4, kMcC = 4;
 __global__ __launch_bounds__(256) void k_mom_corr(const MomCorrInst* __restrict__ mc,
                                                   const double* __restrict__ a, int lda,
                                                   const int32_t* __restrict__ ntr, int bk,
-                                                  int64_t t0) {
+                                                  int64_t t0, unsigned n_tb) {
   const MomCorrInst& M = mc[blockIdx.y];
   const int lane = threadIdx.x & 63;
-  const int j0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * kMcT;
-  const int r0 = blockIdx.z * kMcC;
+  // blockIdx.x: n_tb blocks of times for every four columns
+  const int j0 = ((blockIdx.x % n_tb) * 4 + (threadIdx.x >> 6)) * kMcT;
+  const int r0 = (blockIdx.x / n_tb) * kMcC;
   const int Rg = M.Rg;
   if (j0 >= bk || r0 >= Rg) return;
   const double2* mu = reinterpret_cast<const double2*>(M.mu);
@@ -137,8 +138,14 @@ __global__ __launch_bounds__(256) void k_mom_corr(const MomCorrInst* __restrict_
     }
 }
 
-static dim3 mom_corr_grid(int bk, int n_inst, int rg_max) {
-  return dim3((unsigned)ceil_div(bk, 4 * kMcT), n_inst, (unsigned)ceil_div(rg_max, kMcC));
+// (columns in x too: the conductivity has a column for every energy of every
+// state, more than a grid's y or z hold)
+static void launch_corr_sums(const MomCorrInst* d_mc, int n_inst, const double* d_a, int lda,
+                             const int32_t* d_ntrunc, int bk, int64_t t0, int rg_max,
+                             hipStream_t s) {
+  const unsigned n_tb = (unsigned)ceil_div(bk, 4 * kMcT);
+  const dim3 grid(n_tb * (unsigned)ceil_div(rg_max, kMcC), n_inst);
+  hipLaunchKernelGGL(k_mom_corr, grid, dim3(256), 0, s, d_mc, d_a, lda, d_ntrunc, bk, t0, n_tb);
 }
 
 hipError_t launch_mom_corr(const MomCorrInst* d_mc, int n_inst, int Nk, int halving,
@@ -147,8 +154,7 @@ hipError_t launch_mom_corr(const MomCorrInst* d_mc, int n_inst, int Nk, int halv
   const int na = (Nk + 1) * rg_max;
   hipLaunchKernelGGL(k_mom_assemble, dim3((unsigned)ceil_div(na, 256), n_inst), dim3(256), 0, s,
                      d_mc, Nk, halving);
-  hipLaunchKernelGGL(k_mom_corr, mom_corr_grid(bk, n_inst, rg_max), dim3(256), 0, s, d_mc, d_a,
-                     lda, d_ntrunc, bk, t0);
+  launch_corr_sums(d_mc, n_inst, d_a, lda, d_ntrunc, bk, t0, rg_max, s);
   return hipGetLastError();
 }
 
@@ -157,8 +163,7 @@ hipError_t launch_mom_corr(const MomCorrInst* d_mc, int n_inst, int Nk, int halv
 hipError_t launch_mom_corr_only(const MomCorrInst* d_mc, int n_inst, const double* d_a, int lda,
                                 const int32_t* d_ntrunc, int bk, int64_t t0, int rg_max,
                                 hipStream_t s) {
-  hipLaunchKernelGGL(k_mom_corr, mom_corr_grid(bk, n_inst, rg_max), dim3(256), 0, s, d_mc, d_a,
-                     lda, d_ntrunc, bk, t0);
+  launch_corr_sums(d_mc, n_inst, d_a, lda, d_ntrunc, bk, t0, rg_max, s);
   return hipGetLastError();
 }
 
