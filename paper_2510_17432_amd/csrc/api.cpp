@@ -584,6 +584,12 @@ extern "C" csp_status csp_chebyshev_coefficients(csp_context* c, double x, doubl
 // ------------------------------------------------------------------ recursion helpers
 namespace {
 
+// Kernel form of a stencil lattice.
+int lattice_form(const ChebInst& I) {
+  if (I.kind == CSP_HONEYCOMB) return kLatHoney;
+  return I.Ly == 1 && !I.py ? kLatRow : kLatSquare;
+}
+
 struct ChebPlan {
   int vec = 4;          // values per lane and row (strip = 64 vec)
   int kt = 1;           // steps per launch (temporal blocking)
@@ -665,11 +671,11 @@ ChebPlan plan_cheb(std::vector<ChebInst>& insts, bool fp64, bool mom, int n_cu, 
     const int64_t n = (int64_t)I.Rg * I.n_strips * I.n_segs;
     const int ct = sparse ? I.ell_ct : 0;
     const int64_t nw = sparse ? I.n_segs * ceil_div(I.Rg, ct) : 0;
-    const bool honey = I.kind == CSP_HONEYCOMB;
+    const int lat = lattice_form(I);
     const bool diag = I.eps != nullptr || I.beta0 != 0.0;
-    if (p.runs.empty() || p.runs.back().honey != honey || p.runs.back().diag != diag ||
+    if (p.runs.empty() || p.runs.back().lat != lat || p.runs.back().diag != diag ||
         p.runs.back().sparse != sparse || p.runs.back().ct != ct || p.runs.back().win != win)
-      p.runs.push_back({(int)k, 0, t0, 0, honey, diag, sparse, ct, w0, 0, win, 0});
+      p.runs.push_back({(int)k, 0, t0, 0, lat, diag, sparse, ct, w0, 0, win, 0});
     p.runs.back().n_inst += 1;
     if (win)   // LDS values (window entries x columns) of the run's largest tile
       p.runs.back().win_cap = std::max<int64_t>(p.runs.back().win_cap,
@@ -688,8 +694,7 @@ ChebPlan plan_cheb(std::vector<ChebInst>& insts, bool fp64, bool mom, int n_cu, 
 bool wide_ribbons(const std::vector<ChebInst>& insts, int64_t rows, int n_cu) {
   int64_t waves = 0;
   for (auto& I : insts) {
-    const bool chain = I.Ly == 1 && I.kind != CSP_HONEYCOMB;
-    if (I.kind == CSP_SPARSE || I.py || I.Ly > rows || chain) return false;
+    if (I.kind == CSP_SPARSE || I.py || I.Ly > rows || lattice_form(I) == kLatRow) return false;
     waves += I.Rg * ceil_div(I.opr, 64 * 2 - 2 * cheb_margin(2, 8));
   }
   return waves > 4 * (int64_t)n_cu;
@@ -2320,7 +2325,8 @@ csp_status qe_state_based(csp_context* c, const csp_lattice* L, const void* dev_
   std::vector<ChebInst> sp;
   for (auto& g : groups)
     for (int d = 0; d < 2; ++d) sp.push_back(make_inst(L, g.Rg, fp64, true));
-  ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, recursion_steps(sp, fp64, c->n_cu), 0);
+  ChebPlan sp_plan =
+      plan_cheb(sp, fp64, false, c->n_cu, 2, recursion_steps(sp, fp64, c->n_cu), 0);
   int B64 = 1;
   while (B64 < rows) B64 *= 2;
   const int kcap = fp64 ? (int)((60 * 1024) / (sizeof(double2) * B64)) / 16 * 16 : 240;
@@ -2582,7 +2588,8 @@ extern "C" csp_status csp_quasi_eigenstates(csp_context* c, const csp_lattice* L
   }
   std::vector<ChebInst> sp;
   for (auto& g : groups) sp.push_back(make_inst(L, g.Rg, fp64, true));
-  ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, recursion_steps(sp, fp64, c->n_cu), 0);
+  ChebPlan sp_plan =
+      plan_cheb(sp, fp64, false, c->n_cu, 2, recursion_steps(sp, fp64, c->n_cu), 0);
 
   // Orders per contraction chunk: all of them when they fit, else a multiple
   // of 16 (LDS holds the chunk's coefficients of one energy tile; the ring
@@ -2850,7 +2857,8 @@ extern "C" csp_status csp_ec_correlation(csp_context* c, const csp_lattice* L, i
   }
   std::vector<ChebInst> sp;
   for (auto& g : groups) sp.push_back(make_inst(L, g.Rg, fp64, true));
-  ChebPlan sp_plan = plan_cheb(sp, fp64, false, c->n_cu, 2, recursion_steps(sp, fp64, c->n_cu), 0);
+  ChebPlan sp_plan =
+      plan_cheb(sp, fp64, false, c->n_cu, 2, recursion_steps(sp, fp64, c->n_cu), 0);
   const int64_t target_slices = std::max<int64_t>(1, (int64_t)c->n_cu * 4 / R);
   const int64_t slice_len = std::max<int64_t>(512, (ceil_div(N, target_slices) + 7) / 8 * 8);
   const int n_slices = (int)ceil_div(N, slice_len);

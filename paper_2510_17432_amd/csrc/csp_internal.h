@@ -166,12 +166,18 @@ struct ChebStep {
   int64_t total_items;
 };
 
-// Consecutive instances of one lattice class (honeycomb or not, with or
-// without a diagonal) and their work items; one launch per run.
+// Lattices of the recursion kernel: one open row (a chain) runs without the
+// row loop, in instantiations of its own (as a branch of the square kernel it
+// made launches of 64 x 64 sites 1 % longer).
+constexpr int kLatSquare = 0, kLatHoney = 1, kLatRow = 2;
+
+// Consecutive instances of one lattice class (kernel form, with or without a
+// diagonal) and their work items; one launch per run.
 struct ChebRun {
   int inst0, n_inst;
   int64_t item0, n_items;      // work items (stencil); moment records (explicit matrix)
-  bool honey, diag, sparse;   // diag: on-site energies or H0 != 0
+  int lat;                     // kernel form of the lattice: kLat* (stencil)
+  bool diag, sparse;           // diag: on-site energies or H0 != 0
   int ct;                      // explicit matrix: columns per wave (workgroup if windowed)
   int64_t wave0, n_waves;      // explicit matrix: waves (workgroups if windowed) of the run
   int win;                     // explicit matrix in the windowed layout: rows of a slice (else 0)

@@ -7,7 +7,7 @@
 namespace csp {
 
 #define CSP_CHEB_LAUNCHER(name)                                                                 \
-  hipError_t name(int vec, int kt, bool honey, bool diag, const ChebInst* d_inst, int n_inst,   \
+  hipError_t name(int vec, int kt, int lat, bool diag, const ChebInst* d_inst, int n_inst,   \
                   int64_t item_lo, int64_t item_hi, const ChebStep& st, hipStream_t s);
 CSP_CHEB_LAUNCHER(launch_cheb_f32)
 CSP_CHEB_LAUNCHER(launch_cheb_f32m)
@@ -50,7 +50,7 @@ hipError_t launch_cheb(bool fp64, int vec, int kt, bool mom, bool carry, const C
     hipError_t e;
     if (seq)
       e = r.sparse ? hipErrorInvalidValue
-                   : launch_cheb_f64q(vec, kt, r.honey, r.diag, di, r.n_inst, lo, hi, st, s);
+                   : launch_cheb_f64q(vec, kt, r.lat, r.diag, di, r.n_inst, lo, hi, st, s);
     else if (r.sparse && r.win)
       e = launch_cheb_ellw(fp64, mom, carry, r.ct, r.win, r.win_cap, di, r.n_inst, r.wave0,
                            r.wave0 + r.n_waves, st, s);
@@ -58,15 +58,15 @@ hipError_t launch_cheb(bool fp64, int vec, int kt, bool mom, bool carry, const C
       e = launch_cheb_ell(fp64, mom, carry, r.ct, di, r.n_inst, r.wave0, r.wave0 + r.n_waves, st,
                           s);
     else if (fp64)
-      e = carry  ? launch_cheb_f64mc(vec, kt, r.honey, r.diag, di, r.n_inst, lo, hi, st, s)
-          : self ? launch_cheb_f64s(vec, kt, r.honey, r.diag, di, r.n_inst, lo, hi, st, s)
-          : mom  ? launch_cheb_f64m(vec, kt, r.honey, r.diag, di, r.n_inst, lo, hi, st, s)
-                 : launch_cheb_f64(vec, kt, r.honey, r.diag, di, r.n_inst, lo, hi, st, s);
+      e = carry  ? launch_cheb_f64mc(vec, kt, r.lat, r.diag, di, r.n_inst, lo, hi, st, s)
+          : self ? launch_cheb_f64s(vec, kt, r.lat, r.diag, di, r.n_inst, lo, hi, st, s)
+          : mom  ? launch_cheb_f64m(vec, kt, r.lat, r.diag, di, r.n_inst, lo, hi, st, s)
+                 : launch_cheb_f64(vec, kt, r.lat, r.diag, di, r.n_inst, lo, hi, st, s);
     else
-      e = carry  ? launch_cheb_f32mc(vec, kt, r.honey, r.diag, di, r.n_inst, lo, hi, st, s)
-          : self ? launch_cheb_f32s(vec, kt, r.honey, r.diag, di, r.n_inst, lo, hi, st, s)
-          : mom  ? launch_cheb_f32m(vec, kt, r.honey, r.diag, di, r.n_inst, lo, hi, st, s)
-                 : launch_cheb_f32(vec, kt, r.honey, r.diag, di, r.n_inst, lo, hi, st, s);
+      e = carry  ? launch_cheb_f32mc(vec, kt, r.lat, r.diag, di, r.n_inst, lo, hi, st, s)
+          : self ? launch_cheb_f32s(vec, kt, r.lat, r.diag, di, r.n_inst, lo, hi, st, s)
+          : mom  ? launch_cheb_f32m(vec, kt, r.lat, r.diag, di, r.n_inst, lo, hi, st, s)
+                 : launch_cheb_f32(vec, kt, r.lat, r.diag, di, r.n_inst, lo, hi, st, s);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

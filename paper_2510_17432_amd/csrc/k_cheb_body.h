@@ -329,11 +329,12 @@ template <typename T, int V> __device__ __forceinline__ void any_row(cx<T> (&d)[
 
 // insts: the instances of this launch (consecutive items item_lo..item_hi-1).
 // DIAG: the Hamiltonian has a diagonal (on-site energies, or H0 != 0).
-template <typename T, int V, int KT, bool HONEY, bool DIAG, int MOM, bool CARRY>
+template <typename T, int V, int KT, int LAT, bool DIAG, int MOM, bool CARRY>
 __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts, int n_inst,
                                               int64_t item_lo, int64_t item_hi, ChebStep st) {
   static_assert(V % 2 == 0, "lanes hold whole (even, odd) orbital pairs");
   static_assert(!CARRY || MOM != kMomSelf, "one block with bra = ket carries no state");
+  constexpr bool HONEY = LAT == kLatHoney;
   // sequential form: the recursion with the carried state and, in a time
   // step's last launch, <psi0|carried state>, without moments
   constexpr bool SEQ = CARRY && MOM == kMomNone;
@@ -915,8 +916,8 @@ __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts
   // and no margin rows; a launch is one read of phi_n and phi_{n-1} and the
   // stores.  The row loop takes 2 nlev + 1 iterations for it, and positions
   // one by one (4e6 sites x 4 columns, complex128, MI355X: one block of 32
-  // steps by self products 19.7 -> 5.7 ms, 32 sequential steps 188 -> 51 ms,
-  // two blocks of states 66 -> 37 ms).
+  // steps by self products 19.7 -> 2.7 ms, 32 sequential steps 188 -> 25 ms,
+  // two blocks of states 66 -> 40 ms, 16.9 of them in the recursion: 4 TB/s).
   auto run_chain = [&]() {
     const bool wide = inside || (px && opr % V == 0);
     int wpos[V];
@@ -1071,9 +1072,12 @@ __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts
       if (dots) accq += static_cast<double>(wave_sums<NQ, 32>(sq, lane));
     }
   };
-  if (!HONEY && Ly == 1 && !py) run_chain();
-  else if (whole) run(std::true_type{});
-  else run(std::false_type{});
+  if constexpr (LAT == kLatRow) {
+    run_chain();
+  } else {
+    if (whole) run(std::true_type{});
+    else run(std::false_type{});
+  }
 
   if constexpr (SEQ) {
     if (dot_carry) {                                 // one record per item
@@ -1117,17 +1121,16 @@ __global__ __launch_bounds__(256) void k_cheb(const ChebInst* __restrict__ insts
 
 // Launch helper for one instantiation file: (V, KT) pairs are listed by the
 // including file.
+#define CSP_CHEB_LAUNCH_LAT(T, V, KT, LAT, MOM, CARRY)                                         \
+  do {                                                                                         \
+    if (diag) hipLaunchKernelGGL((cheb::k_cheb<T, V, KT, LAT, true, MOM, CARRY>), grid, block, \
+                                 0, s, d_inst, n_inst, item_lo, item_hi, st);                  \
+    else hipLaunchKernelGGL((cheb::k_cheb<T, V, KT, LAT, false, MOM, CARRY>), grid, block, 0,  \
+                            s, d_inst, n_inst, item_lo, item_hi, st);                          \
+  } while (0)
 #define CSP_CHEB_LAUNCH(T, V, KT, MOM, CARRY)                                                  \
   do {                                                                                         \
-    if (honey) {                                                                               \
-      if (diag) hipLaunchKernelGGL((cheb::k_cheb<T, V, KT, true, true, MOM, CARRY>), grid,     \
-                                   block, 0, s, d_inst, n_inst, item_lo, item_hi, st);         \
-      else hipLaunchKernelGGL((cheb::k_cheb<T, V, KT, true, false, MOM, CARRY>), grid, block,  \
-                              0, s, d_inst, n_inst, item_lo, item_hi, st);                     \
-    } else {                                                                                   \
-      if (diag) hipLaunchKernelGGL((cheb::k_cheb<T, V, KT, false, true, MOM, CARRY>), grid,    \
-                                   block, 0, s, d_inst, n_inst, item_lo, item_hi, st);         \
-      else hipLaunchKernelGGL((cheb::k_cheb<T, V, KT, false, false, MOM, CARRY>), grid, block, \
-                              0, s, d_inst, n_inst, item_lo, item_hi, st);                     \
-    }                                                                                          \
+    if (lat == kLatHoney) CSP_CHEB_LAUNCH_LAT(T, V, KT, kLatHoney, MOM, CARRY);                \
+    else if (lat == kLatRow) CSP_CHEB_LAUNCH_LAT(T, V, KT, kLatRow, MOM, CARRY);               \
+    else CSP_CHEB_LAUNCH_LAT(T, V, KT, kLatSquare, MOM, CARRY);                                \
   } while (0)

@@ -3,7 +3,7 @@
 
 namespace csp {
 
-hipError_t launch_cheb_f32mc(int vec, int kt, bool honey, bool diag, const ChebInst* d_inst, int n_inst,
+hipError_t launch_cheb_f32mc(int vec, int kt, int lat, bool diag, const ChebInst* d_inst, int n_inst,
                              int64_t item_lo, int64_t item_hi, const ChebStep& st, hipStream_t s) {
   const int64_t n = item_hi - item_lo;
   if (n <= 0) return hipSuccess;

@@ -5,13 +5,12 @@ import ctypes
 
 import pytest
 
-import paper_2510_17432_amd as csp
-
 LDS = 80 * 1024
 
 
 @pytest.fixture(scope="module")
 def width():
+    import paper_2510_17432_amd as csp
     # csp::ellw_columns_per_group(bool, bool, int, long, int, long, long)
     f = ctypes.CDLL(csp._lib._name)["_ZN3csp22ellw_columns_per_groupEbbilill"]
     f.restype = ctypes.c_int
