@@ -701,13 +701,25 @@ bool wide_ribbons(const std::vector<ChebInst>& insts, int64_t rows, int n_cu) {
 }
 
 // Steps per launch of the recursion (states, self products): 8, or 4 in
-// complex128 for wide ribbons of up to six rows.  Their rows run in the general
-// form, which computes 2 kt margin rows beside them: honeycomb 300000 x 4 cells
-// x 2 columns, one block of 32 steps by self products 2.42 ms with 8 steps per
-// launch, 1.63 with 4, two blocks of states 12.4 and 12.2 ms; with eight rows
-// the states take 22.1 and 24.0 ms, and 3000 x 4 cells 1.24 and 1.36 ms.
-int recursion_steps(const std::vector<ChebInst>& insts, bool fp64, int n_cu) {
-  return fp64 && wide_ribbons(insts, 6, n_cu) ? 4 : 8;
+// complex128 where eight-step launches of lattices open in y end on the
+// segments at the edges, which run in the general form:
+// - wide ribbons of up to six rows, which compute 2 kt margin rows beside them
+//   (honeycomb 300000 x 4 cells x 2 columns, one block of 32 steps by self
+//   products 2.42 ms with 8 steps per launch, 1.63 with 4, two blocks of states
+//   12.4 and 12.2 ms; with eight rows the states take 22.1 and 24.0 ms, and
+//   3000 x 4 cells 1.24 and 1.36 ms);
+// - lattices in segments of four rows and more than one wave per SIMD, for
+//   states (shorter launches write no less) up to two (honeycomb 400^2 cells x 4
+//   columns, self products 0.87 and 0.61 ms, states 3.59 and 3.67; square 400^2
+//   x 4, 1600 waves: 0.58 and 0.45, 2.21 and 2.09 ms).
+int recursion_steps(std::vector<ChebInst> insts, bool fp64, bool mom, int n_cu) {
+  if (!fp64) return 8;
+  if (wide_ribbons(insts, 6, n_cu)) return 4;
+  for (auto& I : insts)
+    if (I.kind == CSP_SPARSE || I.py || lattice_form(I) == kLatRow) return 8;
+  const ChebPlan p = plan_cheb(insts, true, mom, n_cu, 2, 8);
+  const int64_t simds = 4 * (int64_t)n_cu;
+  return p.seg_rows == 4 && p.total_items > simds && (mom || p.total_items < 2 * simds) ? 4 : 8;
 }
 
 // Bytes of the per-orbital operands that every recursion launch reads once
@@ -1173,7 +1185,7 @@ static csp_status plan_passes(csp_context* c, const std::vector<InstIn>& ins, co
       return (double)seq_workspace(groups, plan);
     }
     const csp_tuning* tune = find_tuning(c, v, fp64, CSP_ASSEMBLE_STATES);
-    int kt = tune ? tune->spmm_steps : recursion_steps(sp, fp64, c->n_cu);
+    int kt = tune ? tune->spmm_steps : recursion_steps(sp, fp64, false, c->n_cu);
     if (fp64) kt = std::min(kt, 4);
     kt = plan_cheb(sp, fp64, false, c->n_cu, tune ? tune->spmm_vec : 0, kt).kt;
     const int b = P.mode == CSP_FP64_SEQ ? 1 : P.block_b > 0 ? P.block_b
@@ -1322,7 +1334,7 @@ static csp_status propagate_impl(csp_context* c, const std::vector<InstIn>& ins,
     sp.push_back(make_inst(ins[g.inst].lat, g.Rg, fp64, true));
     apply_layout(sp.back(), g);
   }
-  int steps = tune ? tune->spmm_steps : recursion_steps(sp, fp64, c->n_cu);
+  int steps = tune ? tune->spmm_steps : recursion_steps(sp, fp64, false, c->n_cu);
   ChebPlan sp_plan;
   int kt = 0, jtiles = 1, K = 0;
 
@@ -1790,7 +1802,7 @@ static csp_status propagate_moments_impl(csp_context* c, const std::vector<InstI
   int vec_want = tune ? tune->spmm_vec : 0;
   // default: 8 steps per launch for the self-product kernels (halving), 4
   // where psi0 or the carried state take registers
-  int kt_want = tune ? tune->spmm_steps : !halving ? 4 : recursion_steps(sp, fp64, c->n_cu);
+  int kt_want = tune ? tune->spmm_steps : !halving ? 4 : recursion_steps(sp, fp64, true, c->n_cu);
   if (carry && !cheb_carry_supported(fp64, 2, kt_want)) kt_want = 4;
   if (carry) vec_want = 2;   // the carried-state kernels hold 2 values per lane
   const int P_batch = 16;
@@ -2326,7 +2338,7 @@ csp_status qe_state_based(csp_context* c, const csp_lattice* L, const void* dev_
   for (auto& g : groups)
     for (int d = 0; d < 2; ++d) sp.push_back(make_inst(L, g.Rg, fp64, true));
   ChebPlan sp_plan =
-      plan_cheb(sp, fp64, false, c->n_cu, 2, recursion_steps(sp, fp64, c->n_cu), 0);
+      plan_cheb(sp, fp64, false, c->n_cu, 2, recursion_steps(sp, fp64, false, c->n_cu), 0);
   int B64 = 1;
   while (B64 < rows) B64 *= 2;
   const int kcap = fp64 ? (int)((60 * 1024) / (sizeof(double2) * B64)) / 16 * 16 : 240;
@@ -2589,7 +2601,7 @@ extern "C" csp_status csp_quasi_eigenstates(csp_context* c, const csp_lattice* L
   std::vector<ChebInst> sp;
   for (auto& g : groups) sp.push_back(make_inst(L, g.Rg, fp64, true));
   ChebPlan sp_plan =
-      plan_cheb(sp, fp64, false, c->n_cu, 2, recursion_steps(sp, fp64, c->n_cu), 0);
+      plan_cheb(sp, fp64, false, c->n_cu, 2, recursion_steps(sp, fp64, false, c->n_cu), 0);
 
   // Orders per contraction chunk: all of them when they fit, else a multiple
   // of 16 (LDS holds the chunk's coefficients of one energy tile; the ring
@@ -2858,7 +2870,7 @@ extern "C" csp_status csp_ec_correlation(csp_context* c, const csp_lattice* L, i
   std::vector<ChebInst> sp;
   for (auto& g : groups) sp.push_back(make_inst(L, g.Rg, fp64, true));
   ChebPlan sp_plan =
-      plan_cheb(sp, fp64, false, c->n_cu, 2, recursion_steps(sp, fp64, c->n_cu), 0);
+      plan_cheb(sp, fp64, false, c->n_cu, 2, recursion_steps(sp, fp64, false, c->n_cu), 0);
   const int64_t target_slices = std::max<int64_t>(1, (int64_t)c->n_cu * 4 / R);
   const int64_t slice_len = std::max<int64_t>(512, (ceil_div(N, target_slices) + 7) / 8 * 8);
   const int n_slices = (int)ceil_div(N, slice_len);
