@@ -392,8 +392,15 @@ extern "C" csp_status csp_lattice_create_sparse(csp_context* c, int64_t N, int32
     // Slices of 256 rows (windows 1.45 times those of 128 where the matrix is
     // local, so fewer values staged per row and more rows on a CU) are taken
     // for matrices that the 256 MB of last-level cache do not hold beside the
-    // vectors, from 160 MB in complex64 on: 1500^2 rows at D = 121, 5 columns
-    // 23.3 -> 21.9 ms for 16 time steps, 512^2 rows 10.8 -> 10.2 ms for 64.
+    // vectors, from 160 MB in complex64 on.  A matrix is laid out before the
+    // columns it will meet are known, and the sides differ by their number:
+    // 24 time steps of moments, 256 against 128 rows, D = 121, complex64
+    // 600^2 rows 3.57 / 3.45 ms with 1 column, 5.53 / 4.79 with 3, 6.44 /
+    // 7.58 with 5; 700^2 rows 4.43 / 4.53, 6.17 / 5.83, 8.03 / 8.14; over 420^2
+    // to 900^2 rows 0.95-1.16 of the 128-row time with 1 to 4 columns (450^2
+    // up to 1.33), 0.83-1.03 with 5 to 10 (512^2 with 10: 1.18).  In
+    // complex128 0.85-1.08 with 1 to 3 columns, 0.84-1.03 with 4 to 10 (420^2
+    // with 5: 1.11, 450^2 with 6: 1.07); D = 61, 0.92-1.09.
     // Below, the grid needs the 128-row workgroups (200^2 rows, 5 columns 4.0
     // against 4.1 ms, 350^2, 4 columns 4.7 against 5.1 ms), and where windows
     // pass 800 positions fewer workgroups fit a CU (512^2 rows at D = 233, 2
@@ -1800,8 +1807,8 @@ static csp_status propagate_moments_impl(csp_context* c, const std::vector<InstI
   }
   const csp_tuning* tune = find_tuning(c, ins, fp64, CSP_ASSEMBLE_MOMENTS);
   int vec_want = tune ? tune->spmm_vec : 0;
-  // default: 8 steps per launch for the self-product kernels (halving), 4
-  // where psi0 or the carried state take registers
+  // default: 4 steps per launch where psi0 or the carried state take
+  // registers, else (halving, self products) by recursion_steps
   int kt_want = tune ? tune->spmm_steps : !halving ? 4 : recursion_steps(sp, fp64, true, c->n_cu);
   if (carry && !cheb_carry_supported(fp64, 2, kt_want)) kt_want = 4;
   if (carry) vec_want = 2;   // the carried-state kernels hold 2 values per lane
@@ -2054,8 +2061,8 @@ static csp_status propagate_moments_impl(csp_context* c, const std::vector<InstI
 // recursion's epilogue adds c_n phi_n to the next state as the orders are
 // produced, and the step's last launch also sums <psi0|psi(t_j)>, so the
 // orders are never stored beyond the two that a launch hands to the next:
-// with 20 orders and five steps per launch 21 vectors move per time step,
-// against 51 with a ring of orders and a contraction.
+// with 20 orders in three launches of up to seven steps 16 vectors move per
+// time step, against 51 with a ring of orders and a contraction.
 static csp_status propagate_seq_impl(csp_context* c, const std::vector<InstIn>& ins,
                                      const csp_params& P, double t_start, csp_report* rep) {
   for (size_t i = 0; i < ins.size(); ++i)

@@ -21,7 +21,9 @@
 // lane's own registers except at its two ends, which come from the adjacent
 // lane by a DPP wavefront shift.  On the honeycomb lattice the vertical
 // partner of an orbital is the other orbital of its (even, odd) pair one row
-// up or down, which is in the same lane (V is even, p0 is even).
+// up or down, which is in the same lane (V is even, p0 is even).  A lattice
+// of one row has no vertical neighbours: it runs in instantiations of its own
+// (kLatRow) whose levels follow one another in registers without a row loop.
 //
 // The strip covers [os - MG, os - MG + 64 V); each level is valid one
 // position further inside on each side than the one before, so after up to

@@ -286,8 +286,9 @@ __global__ __launch_bounds__(kContractThreads) __attribute__((amdgpu_waves_per_e
 // are those of k_contract_f32: the results are bit-identical.  Measured
 // (complex64 states, b = 32): square 4099^2, 3 columns, 80 steps 78.8 -> 74.8
 // ms; graphene 1024^2, 68 columns, 64 steps 135.9 -> 134.2 ms (28.9 ms a
-// launch of 172 GB, 5.95 TB/s).  Three stages (two workgroups per CU instead
-// of three) gave nothing.
+// launch of 172 GB, 5.95 TB/s).  At those 149 orders a workgroup takes 58 KB
+// (20 KB of coefficients, 36 KB of stages), two per CU; three fit from 112
+// orders down.  Three stages gave nothing.
 //
 // Waits.  A wave reads only what it loaded itself, so no barrier is needed:
 // loads complete in issue order, stage s has landed once at most the

@@ -24,8 +24,8 @@
 // load instruction whose lanes each read a different order would touch 32
 // pages), and each of its four waves multiplies one tile of 32 orders.
 // The FP32 tiles of all slices are summed in FP64 in slice order (no
-// atomics).  The FP64 path stages the same tiles and forms the sums with
-// FMAs.  m_n = conj(mu_n).
+// atomics).  The FP64 path stages the same tiles and forms the sums on
+// v_mfma_f64_16x16x4.  m_n = conj(mu_n).
 #include "csp_internal.h"
 
 namespace csp {
