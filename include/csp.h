@@ -238,7 +238,8 @@ csp_status csp_lattice_create(csp_context *ctx, const csp_lattice_desc *desc,
  * applies one Chebyshev step per launch (a gathered sparse product).  When
  * at least half of the slices of 128 rows, regrouped to be compact in the
  * matrix graph, name at most 2048 distinct columns that each serve four or
- * more entries, a second, windowed copy of the matrix is kept (rows per
+ * more entries (matrices of 160 MB and more in complex64: 256 rows, where half
+ * of those slices name at most 800), a second, windowed copy of the matrix is kept (rows per
  * slice, 16-bit window-local and 32-bit global columns, FP64 and FP32
  * values: 18 B per entry, rows padded to a multiple of 4 entries, besides
  * the 16 of the slice layout) and the recursion stages each slice's window
